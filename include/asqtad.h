@@ -161,6 +161,17 @@ int asq_gauge_destroy(asq_gauge* g);
 int asqtad_build_links(const int dims[4], const double* thin_dev, double u0, double* fat_dev, double* long_dev,
                        void* hip_stream);
 
+/* The same with a workspace, in which every staple that several paths share is
+   formed once (2.5 times fewer products).  work_dev: caller-owned, at least
+   asqtad_links_workspace_bytes(dims) bytes (0 for invalid extents or 2^28 sites
+   or more, which only asqtad_build_links takes), 256-byte aligned, disjoint from
+   the links, overwritten; it must stay until the enqueued work is done.  The
+   links agree with asqtad_build_links to FP64 rounding (the sums are ordered
+   differently).  ASQ_ENOMEM if the workspace is too small. */
+size_t asqtad_links_workspace_bytes(const int dims[4]);
+int asqtad_build_links_work(const int dims[4], const double* thin_dev, double u0, double* fat_dev, double* long_dev,
+                            void* work_dev, size_t work_bytes, void* hip_stream);
+
 /* Device workspace bytes of asqtad_plaquette for these extents (0 if invalid). */
 size_t asqtad_plaquette_workspace_bytes(const int dims[4]);
 /* Mean plaquette of thin links, the input of the tadpole factor u0 = P^(1/4)

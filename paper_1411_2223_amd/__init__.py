@@ -95,6 +95,9 @@ _SIGS = {
                                   ctypes.POINTER(ctypes.c_double)]),
     "serve_destroy": (ctypes.c_int, [_vp]),
     "asqtad_build_links": (ctypes.c_int, [ctypes.POINTER(ctypes.c_int), _vp, ctypes.c_double, _vp, _vp, _vp]),
+    "asqtad_links_workspace_bytes": (ctypes.c_size_t, [ctypes.POINTER(ctypes.c_int)]),
+    "asqtad_build_links_work": (ctypes.c_int, [ctypes.POINTER(ctypes.c_int), _vp, ctypes.c_double, _vp, _vp, _vp,
+                                               ctypes.c_size_t, _vp]),
     "asqtad_plaquette_workspace_bytes": (ctypes.c_size_t, [ctypes.POINTER(ctypes.c_int)]),
     "asqtad_plaquette": (ctypes.c_int, [ctypes.POINTER(ctypes.c_int), _vp, _vp, ctypes.c_size_t,
                                         ctypes.POINTER(ctypes.c_double), _vp]),
@@ -215,6 +218,22 @@ def empty_bytes(n, device="cuda"):
     return t
 
 
+def _stream_scratch(nbytes, device, stream):
+    """A device buffer that the work about to be enqueued on `stream` uses and nothing after it: it
+    belongs to that stream in the caching allocator, so it may be dropped as soon as the work is
+    enqueued.  None if nbytes is 0, the stream is not a torch stream of that device, or the
+    device has no room for it."""
+    torch = _torch()
+    stream = torch.cuda.current_stream() if stream is None else stream
+    if nbytes == 0 or getattr(stream, "device", None) != device:
+        return None
+    try:
+        with torch.cuda.stream(stream):
+            return empty_bytes(nbytes, device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def empty_vec(nsites, prec="f64", device="cuda"):
     """A device tensor holding nsites canonical colour-vector records of tier prec."""
     torch = _torch()
@@ -287,9 +306,15 @@ def build_links(dims, thin_dev, u0=1.0, fat=None, lng=None, stream=None):
     for t in (fat, lng):
         if t.dtype != torch.float64 or t.numel() != n or not t.is_contiguous():
             raise AsqError(ASQ_EINVAL, "build_links: outputs must be contiguous float64 tensors of V*4*18 reals")
-    rc = asqtad_build_links((ctypes.c_int * 4)(*dims), thin_dev.data_ptr(), float(u0), fat.data_ptr(),
-                            lng.data_ptr(), stream_ptr(stream))
-    check(rc, "asqtad_build_links")
+    d4 = (ctypes.c_int * 4)(*dims)
+    work = _stream_scratch(asqtad_links_workspace_bytes(d4), thin_dev.device, stream)
+    if work is None:
+        rc = asqtad_build_links(d4, thin_dev.data_ptr(), float(u0), fat.data_ptr(), lng.data_ptr(), stream_ptr(stream))
+        check(rc, "asqtad_build_links")
+    else:
+        rc = asqtad_build_links_work(d4, thin_dev.data_ptr(), float(u0), fat.data_ptr(), lng.data_ptr(),
+                                     work.data_ptr(), work.numel(), stream_ptr(stream))
+        check(rc, "asqtad_build_links_work")
     return fat, lng
 
 

@@ -20,7 +20,8 @@
 // cN = -1/(24 u0^2); u0 is the tadpole factor.  Links are periodic in every
 // direction (the time-boundary sign is applied when the links are imported).
 //
-// Three launches on the caller's stream:
+// asqtad_build_links_work forms the shared staples once in a caller's workspace
+// (below).  asqtad_build_links has no workspace: three launches on the stream:
 //   1. a site-fastest copy of the thin links, written into the long-link output
 //      (used as scratch, so the call needs no workspace);
 //   2. the fat links: a block covers 64 sites (lane = site) for one mu, so mu is
@@ -30,12 +31,14 @@
 //      links, which come from L2);
 //   3. the long links from the canonical thin links, overwriting the copy.
 // Per (site, mu) the fat link takes 12 x (4 + 2 x 4) + 6 x 2 = 156 SU(3)
-// products (the two orders of a {nu, rho} group share their core) and the
+// products there (the two orders of a {nu, rho} group share their core) and the
 // long link 2.
 #include <math.h>
+#include <string.h>
 
 #include <map>
 #include <mutex>
+#include <string>
 
 #include "asq_reduce.h"
 
@@ -140,6 +143,25 @@ __device__ __forceinline__ void acc_nn(M3& C, double s, const M3& A, const M3& B
       C.e[a][b].re = fmaR(s, v.re, C.e[a][b].re);
       C.e[a][b].im = fmaR(s, v.im, C.e[a][b].im);
     }
+}
+
+// C += A B^dag and C += A B, a column of the inner sum at a time
+__device__ __forceinline__ void acc_nd1(M3& C, const M3& A, const M3& B) {
+#pragma unroll
+  for (int b = 0; b < 3; ++b)
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) cmac_conj(C.e[a][b], B.e[b][k], A.e[a][k]);
+}
+
+__device__ __forceinline__ void acc_nn1(M3& C, const M3& A, const M3& B) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) cmac(C.e[a][b], A.e[a][k], B.e[k][b]);
 }
 
 __device__ __forceinline__ M3 scaled(double s, const M3& X) {
@@ -301,11 +323,244 @@ __global__ void __launch_bounds__(256) fatten_kernel(const FattenArgs A) {
   }
 }
 
+// ---- with a workspace: three stages of shared staples ------------------------
+// The nested sum shares its inner staples between paths.  With room for them,
+// each is formed once: for every mu and axis c off mu
+//   core_c(z) = c5 U_mu(z) + c7 sum_+-c T_d(U_mu)(z)                        (stage 1)
+//   v_nu(y)   = c3 U_mu(y) + sum_{rho != nu} sum_+-rho T_d(core_c)(y),
+//               c the axis that is left                                     (stage 2)
+//   F_mu(x)   = c1 U_mu(x) + sum_+-nu T_d(v_nu + cL T_d(U_mu))(x)           (stage 3)
+// 12 + 24 + 24 = 60 products per (site, mu) instead of 156.
+constexpr long kStageMaxSites = (1L << 28) - 1;  // site indices, and differences of them, in 32 bits
+// All four directions per launch, 4032 workspace bytes per site, up to 4 GiB of
+// workspace; beyond, one direction at a time in 1440 bytes per site (0.46 ms more
+// at 20^3 x 64, measured with a thread per (site, mu)).
+constexpr long kStageAllMuSites = (4L << 30) / 4032;
+struct StageArgs {
+  int d[4], s[4];       // extents and lexicographic strides
+  int n;                // sites
+  int mu0, nmu;         // the directions of this launch: one, or all four (a wave each)
+  const double2* soa;   // thin links, 4 slots
+  double2* core;        // 3 nmu slots: per direction, by position of c among the axes off mu
+  double2* v;           // 3 nmu slots: per direction, by position of nu
+  double2* fat;         // canonical outputs
+  double2* lng;
+  double c1, c3, c5, c7, cL, cN;
+};
+
+struct Pos {
+  int i, x[4];  // lexicographic index and coordinates
+};
+
+__device__ __forceinline__ void stage_coords(const StageArgs& A, int i, Pos& p) {
+  p.i = i;
+  unsigned r = (unsigned)i;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    p.x[a] = (int)(r % (unsigned)A.d[a]);
+    r /= (unsigned)A.d[a];
+  }
+  p.x[3] = (int)r;
+}
+
+// (mu, site, part) of this thread.  A block is four waves: the four directions
+// over the same 64 sites, or 256 sites of one direction; `parts` blocks next to
+// each other in dispatch order share its sites.
+__device__ __forceinline__ bool stage_site(const StageArgs& A, int parts, int& mu, int& m, int& part, Pos& p) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lin = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+  const int blk = lin / parts;
+  part = lin % parts;
+  m = A.nmu == 4 ? wave : 0;
+  mu = A.mu0 + m;
+  const int site = A.nmu == 4 ? blk * 64 + ((int)threadIdx.x & 63) : blk * 256 + (int)threadIdx.x;
+  stage_coords(A, min(site, A.n - 1), p);  // lanes past the end copy the last site
+  return site < A.n;
+}
+
+__device__ __forceinline__ int coord(const Pos& p, int ax) {
+  return ax == 0 ? p.x[0] : (ax == 1 ? p.x[1] : (ax == 2 ? p.x[2] : p.x[3]));
+}
+
+// Index change of a hop of h (|h| <= 2) along ax from p.
+__device__ __forceinline__ int hop(const StageArgs& A, const Pos& p, int ax, int h) {
+  const int c = coord(p, ax) + h, L = A.d[ax];
+  return (h + (c >= L ? -L : (c < 0 ? L : 0))) * A.s[ax];
+}
+
+// The workspace arrays hold `slots` matrices per site in blocks of 64 sites,
+// [site block][slot][9][64]: a wave's 1 KB rows of one matrix lie together.  (As
+// rows of the whole lattice the nine entries of a matrix are a multiple of 4 KB
+// apart on most lattices: the same memory channels, and nine pages.)
+typedef double d2v __attribute__((ext_vector_type(2)));
+struct Slots {
+  const double2* base;
+  int slots, slot;
+  __device__ __forceinline__ size_t at(int i) const {
+    return ((size_t)(unsigned)(i >> 6) * slots + slot) * (9 * kFatSites) + (i & 63);
+  }
+};
+
+__device__ __forceinline__ M3 slot_load(const Slots& s, int i) {
+  const double2* q = s.base + s.at(i);
+  M3 U;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const double2 v = q[k * kFatSites];
+    U.e[k / 3][k % 3].re = v.x;
+    U.e[k / 3][k % 3].im = v.y;
+  }
+  return U;
+}
+
+__device__ __forceinline__ void slot_store(const Slots& s, int i, const M3& U) {
+  double2* q = const_cast<double2*>(s.base) + s.at(i);
+#pragma unroll
+  for (int k = 0; k < 9; ++k)
+    __builtin_nontemporal_store((d2v){U.e[k / 3][k % 3].re, U.e[k / 3][k % 3].im},
+                                reinterpret_cast<d2v*>(q + k * kFatSites));
+}
+
+__device__ __forceinline__ Slots link_slot(const StageArgs& A, int mu) { return {A.soa, 4, mu}; }
+// the arrays of stages 1 and 2: slot q of direction m of this launch
+__device__ __forceinline__ Slots stage_slot(const StageArgs& A, const double2* base, int m, int q) {
+  return {base, 3 * A.nmu, 3 * m + q};
+}
+
+// C += W X W2^dag (neg = false) or W^dag X W2 with W, W2 the matrices of a slot at
+// sites w and w2.  The inner product is formed whole before W2 is needed: 224 and
+// 208 registers instead of 226 and 210 with both factors live, 0.42 against 0.45 ms
+// for the core stage at 20^3 x 64.
+__device__ __forceinline__ void add_staple(M3& C, bool neg, const Slots& L, int w, const M3& X, int w2) {
+  const M3 W = slot_load(L, w);
+  M3 P;
+  if (!neg) {
+    P = mul_nn(W, X);
+    acc_nd1(C, P, slot_load(L, w2));
+  } else {
+    P = mul_dn(W, X);
+    acc_nn1(C, P, slot_load(L, w2));
+  }
+}
+
+// C += T_d(X)(p), d = +-ax, X the matrices of a slot.
+__device__ __forceinline__ void add_slot_staple(const StageArgs& A, M3& C, const Pos& p, int mu, int ax, bool neg,
+                                                const Slots& X) {
+  const int h = hop(A, p, ax, neg ? -1 : 1), fwd = hop(A, p, mu, 1);
+  const int w = neg ? p.i + h : p.i;
+  add_staple(C, neg, link_slot(A, ax), w, slot_load(X, p.i + h), w + fwd);
+}
+
+__device__ __forceinline__ M3 zero_m3() {
+  M3 C;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) C.e[k / 3][k % 3] = {0.0, 0.0};
+  return C;
+}
+
+// C = s C + t U
+__device__ __forceinline__ void scale_add(M3& C, double s, double t, const M3& U) {
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    cx<double>& c = C.e[k / 3][k % 3];
+    c.re = fmaR(t, U.e[k / 3][k % 3].re, s * c.re);
+    c.im = fmaR(t, U.e[k / 3][k % 3].im, s * c.im);
+  }
+}
+
+// the q-th axis off mu
+__device__ __forceinline__ int axis_off(int mu, int q) { return q + (q >= mu ? 1 : 0); }
+
+__global__ void __launch_bounds__(256) fat_core_kernel(const StageArgs A) {
+  int mu, m, q;
+  Pos p;
+  const bool valid = stage_site(A, 3, mu, m, q, p);
+  const Slots U = link_slot(A, mu);
+  M3 C = zero_m3();
+#pragma unroll 1
+  for (int sn = 0; sn < 2; ++sn) add_slot_staple(A, C, p, mu, axis_off(mu, q), sn != 0, U);
+  scale_add(C, A.c7, A.c5, slot_load(U, p.i));
+  if (valid) slot_store(stage_slot(A, A.core, m, q), p.i, C);
+}
+
+__global__ void __launch_bounds__(256) fat_five_kernel(const StageArgs A) {
+  int mu, m, q;  // q: nu
+  Pos p;
+  const bool valid = stage_site(A, 3, mu, m, q, p);
+  M3 C = zero_m3();
+#pragma unroll 1
+  for (int r = 0; r < 4; ++r) {  // rho = q + 1, q + 2 (mod 3), both signs; c the axis left
+    const int rho = (q + 1 + (r >> 1)) % 3, c = 3 - q - rho;
+    add_slot_staple(A, C, p, mu, axis_off(mu, rho), (r & 1) != 0, stage_slot(A, A.core, m, c));
+  }
+  scale_add(C, 1.0, A.c3, slot_load(link_slot(A, mu), p.i));
+  if (valid) slot_store(stage_slot(A, A.v, m, q), p.i, C);
+}
+
+// One wave per nu (three per block) over 64 sites of one mu; the waves meet in LDS.
+__global__ void __launch_bounds__(192) fat_link_kernel(const StageArgs A) {
+  __shared__ double2 part[3][9][kFatSites];
+  const int lane = threadIdx.x & 63;
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lin = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+  const int m = lin % A.nmu, mu = A.mu0 + m;
+  const int s0 = lin / A.nmu * kFatSites;
+  Pos p;
+  stage_coords(A, min(s0 + lane, A.n - 1), p);
+  const Slots U = link_slot(A, mu);
+  const int nu = axis_off(mu, q);
+  const Slots W = link_slot(A, nu);
+  M3 F = zero_m3();
+#pragma unroll 1
+  for (int sn = 0; sn < 2; ++sn) {
+    const bool neg = sn != 0;
+    const int h1 = hop(A, p, nu, neg ? -1 : 1), h2 = hop(A, p, nu, neg ? -2 : 2), fwd = hop(A, p, mu, 1);
+    // v_nu + cL T_d(U_mu) at y = x + d
+    M3 X = zero_m3();
+    const int wi = p.i + (neg ? h2 : h1);  // the inner staple's links start at y, or at y - |d|
+    add_staple(X, neg, W, wi, slot_load(U, p.i + h2), wi + fwd);
+    scale_add(X, A.cL, 1.0, slot_load(stage_slot(A, A.v, m, q), p.i + h1));
+    const int wo = p.i + (neg ? h1 : 0);
+    add_staple(F, neg, W, wo, X, wo + fwd);
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) part[q][k][lane] = make_double2(F.e[k / 3][k % 3].re, F.e[k / 3][k % 3].im);
+  __syncthreads();
+  // fat links of the block's sites: 144 bytes per site of the canonical output
+  for (int e = threadIdx.x; e < 9 * kFatSites; e += 192) {
+    const int j = e / 9, k = e % 9;
+    if (s0 + j >= A.n) break;
+    const double2 u = (U.base + U.at(s0 + j))[k * kFatSites];
+    const double2 a = part[0][k][j], b = part[1][k][j], c = part[2][k][j];
+    A.fat[((size_t)(s0 + j) * 4 + mu) * 9 + k] =
+        make_double2(fmaR(A.c1, u.x, a.x + b.x + c.x), fmaR(A.c1, u.y, a.y + b.y + c.y));
+  }
+}
+
+// L_mu(x) = cN U_mu(x) U_mu(x+mu) U_mu(x+2mu) from the site-fastest copy, a wave per mu.
+__global__ void __launch_bounds__(256) long_soa_kernel(const StageArgs A) {
+  int mu, m, part;
+  Pos p;
+  stage_site(A, 1, mu, m, part, p);
+  const Slots U = link_slot(A, mu);
+  M3 L = zero_m3();
+  const M3 P = mul_nn(slot_load(U, p.i), slot_load(U, p.i + hop(A, p, mu, 1)));
+  acc_nn(L, A.cN, P, slot_load(U, p.i + hop(A, p, mu, 2)));
+  __shared__ double2 tile[kFatSites][37];
+#pragma unroll
+  for (int k = 0; k < 9; ++k)
+    tile[threadIdx.x & 63][mu * 9 + k] = make_double2(L.e[k / 3][k % 3].re, L.e[k / 3][k % 3].im);
+  __syncthreads();
+  const int s0 = xcd_remap((int)blockIdx.x, (int)gridDim.x) * kFatSites;
+  const int nrun = min(kFatSites, A.n - s0) * 36;
+  for (int e = threadIdx.x; e < nrun; e += 256) A.lng[(size_t)s0 * 36 + e] = tile[e / 36][e % 36];
+}
+
 // Canonical thin links -> the site-fastest copy.  A block moves 64 sites: it
 // reads their 36 complex entries each as one contiguous 36 KB run and writes 36
 // rows of 64 entries, both coalesced, through LDS.
 __global__ void __launch_bounds__(256) thin_soa_kernel(const double2* __restrict__ thin, double2* __restrict__ soa,
-                                                       long V) {
+                                                       long V, bool blocked) {
   __shared__ double2 tile[36][kFatSites + 1];
   const long s0 = (long)blockIdx.x * kFatSites;
   const int n = (int)(V - s0 < kFatSites ? V - s0 : kFatSites);
@@ -313,7 +568,7 @@ __global__ void __launch_bounds__(256) thin_soa_kernel(const double2* __restrict
   __syncthreads();
   for (int e = threadIdx.x; e < 36 * kFatSites; e += blockDim.x) {
     const int j = e / kFatSites, i = e % kFatSites;
-    if (i < n) soa[(size_t)j * V + s0 + i] = tile[j][i];
+    if (i < n) soa[blocked ? s0 * 36 + e : (size_t)j * V + s0 + i] = tile[j][i];
   }
 }
 
@@ -411,32 +666,42 @@ bool overlaps(const void* a, const void* b, size_t n) {
 
 using namespace asq;
 
-extern "C" int asqtad_build_links(const int dims[4], const double* thin_dev, double u0, double* fat_dev,
-                                  double* long_dev, void* hip_stream) {
+// Bytes of one workspace slot (a 3 x 3 complex matrix per site, in whole site blocks).
+static size_t slot_bytes(long V) { return align_up((size_t)V, kFatSites) * 9 * sizeof(double2); }
+
+extern "C" size_t asqtad_links_workspace_bytes(const int dims[4]) {
+  if (!valid_extents(dims)) return 0;
+  const long V = (long)dims[0] * dims[1] * dims[2] * dims[3];
+  if (V > kStageMaxSites) return 0;
+  return (4 + 6 * (V <= kStageAllMuSites ? 4 : 1)) * slot_bytes(V);
+}
+
+// Shared checks of the two entry points; fills the coefficients.
+static int links_args(const char* who, const int dims[4], const double* thin_dev, double u0, double* fat_dev,
+                      double* long_dev, FattenArgs& a) {
   if (!dims || !thin_dev || !fat_dev || !long_dev) {
-    set_last_error("asqtad_build_links: null pointer");
+    set_last_error(std::string(who) + ": null pointer");
     return ASQ_EINVAL;
   }
   if (!valid_extents(dims)) {
-    set_last_error("asqtad_build_links: extents must be even and >= 4, the lattice not too large");
+    set_last_error(std::string(who) + ": extents must be even and >= 4, the lattice not too large");
     return ASQ_EINVAL;
   }
   const long V = (long)dims[0] * dims[1] * dims[2] * dims[3];
   if (!(u0 > 0) || !isfinite(u0)) {
-    set_last_error("asqtad_build_links: u0 must be positive and finite");
+    set_last_error(std::string(who) + ": u0 must be positive and finite");
     return ASQ_EINVAL;
   }
   if (((uintptr_t)thin_dev & 15) || ((uintptr_t)fat_dev & 15) || ((uintptr_t)long_dev & 15)) {
-    set_last_error("asqtad_build_links: link arrays must be 16-byte aligned");
+    set_last_error(std::string(who) + ": link arrays must be 16-byte aligned");
     return ASQ_EINVAL;
   }
   const size_t bytes = (size_t)V * 4 * 18 * sizeof(double);
   if (overlaps(thin_dev, fat_dev, bytes) || overlaps(thin_dev, long_dev, bytes) ||
       overlaps(fat_dev, long_dev, bytes)) {
-    set_last_error("asqtad_build_links: thin, fat and long arrays must not overlap");
+    set_last_error(std::string(who) + ": thin, fat and long arrays must not overlap");
     return ASQ_EINVAL;
   }
-  FattenArgs a;
   for (int mu = 0; mu < 4; ++mu) a.d[mu] = dims[mu];
   a.V = V;
   a.thin = (const double2*)thin_dev;
@@ -449,15 +714,82 @@ extern "C" int asqtad_build_links(const int dims[4], const double* thin_dev, dou
   a.c7 = 1.0 / (384.0 * u6);
   a.cL = -1.0 / (16.0 * u4);
   a.cN = -1.0 / (24.0 * u2);
+  return ASQ_OK;
+}
+
+extern "C" int asqtad_build_links(const int dims[4], const double* thin_dev, double u0, double* fat_dev,
+                                  double* long_dev, void* hip_stream) {
+  FattenArgs a;
+  if (const int rc = links_args("asqtad_build_links", dims, thin_dev, u0, fat_dev, long_dev, a)) return rc;
   // The long-link output holds the site-fastest copy of the thin links while the
   // fat links are built; the long links overwrite it last.
   a.soa = (const double2*)long_dev;
   hipStream_t s = (hipStream_t)hip_stream;
-  thin_soa_kernel<<<(unsigned)((V + kFatSites - 1) / kFatSites), 256, 0, s>>>(a.thin, (double2*)long_dev, V);
+  thin_soa_kernel<<<(unsigned)((a.V + kFatSites - 1) / kFatSites), 256, 0, s>>>(a.thin, (double2*)long_dev, a.V, false);
   ASQ_HIP_TRY(hipGetLastError());
-  fatten_kernel<<<(unsigned)(4 * ((V + kFatSites - 1) / kFatSites)), 256, 0, s>>>(a);
+  fatten_kernel<<<(unsigned)(4 * ((a.V + kFatSites - 1) / kFatSites)), 256, 0, s>>>(a);
   ASQ_HIP_TRY(hipGetLastError());
-  long_link_kernel<<<(unsigned)((V * 4 + 255) / 256), 256, 0, s>>>(a);
+  long_link_kernel<<<(unsigned)((a.V * 4 + 255) / 256), 256, 0, s>>>(a);
+  ASQ_HIP_TRY(hipGetLastError());
+  return ASQ_OK;
+}
+
+extern "C" int asqtad_build_links_work(const int dims[4], const double* thin_dev, double u0, double* fat_dev,
+                                       double* long_dev, void* work_dev, size_t work_bytes, void* hip_stream) {
+  const char* who = "asqtad_build_links_work";
+  FattenArgs f;
+  if (const int rc = links_args(who, dims, thin_dev, u0, fat_dev, long_dev, f)) return rc;
+  const size_t need = asqtad_links_workspace_bytes(dims);
+  if (!work_dev || !need || ((uintptr_t)work_dev & 255)) {
+    set_last_error(std::string(who) + ": null or misaligned workspace (256 bytes), or more than 2^28 - 1 sites");
+    return ASQ_EINVAL;
+  }
+  if (work_bytes < need) {
+    set_last_error(std::string(who) + ": workspace smaller than asqtad_links_workspace_bytes()");
+    return ASQ_ENOMEM;
+  }
+  const size_t bytes = (size_t)f.V * 4 * 18 * sizeof(double);
+  for (const void* q : {(const void*)thin_dev, (const void*)fat_dev, (const void*)long_dev})
+    if ((uintptr_t)q < (uintptr_t)work_dev + work_bytes && (uintptr_t)work_dev < (uintptr_t)q + bytes) {
+      set_last_error(std::string(who) + ": the workspace must not overlap the links");
+      return ASQ_EINVAL;
+    }
+  StageArgs a;
+  memset(&a, 0, sizeof(a));
+  for (int mu = 0; mu < 4; ++mu) a.d[mu] = f.d[mu];
+  a.s[0] = 1;
+  for (int mu = 1; mu < 4; ++mu) a.s[mu] = a.s[mu - 1] * a.d[mu - 1];
+  a.n = (int)f.V;
+  const size_t slot = slot_bytes(f.V);
+  double2* soa = (double2*)work_dev;
+  a.soa = soa;
+  a.nmu = f.V <= kStageAllMuSites ? 4 : 1;
+  a.core = (double2*)((char*)work_dev + 4 * slot);
+  a.v = (double2*)((char*)work_dev + (4 + 3 * a.nmu) * slot);
+  a.fat = f.fat;
+  a.lng = f.lng;
+  a.c1 = f.c1;
+  a.c3 = f.c3;
+  a.c5 = f.c5;
+  a.c7 = f.c7;
+  a.cL = f.cL;
+  a.cN = f.cN;
+  hipStream_t s = (hipStream_t)hip_stream;
+  const unsigned nb64 = (unsigned)((f.V + kFatSites - 1) / kFatSites);
+  const unsigned nb = a.nmu == 4 ? nb64 : (unsigned)((f.V + 255) / 256);
+  thin_soa_kernel<<<nb64, 256, 0, s>>>(f.thin, soa, f.V, true);
+  ASQ_HIP_TRY(hipGetLastError());
+  for (a.mu0 = 0; a.mu0 < 4; a.mu0 += a.nmu) {
+    fat_core_kernel<<<3 * nb, 256, 0, s>>>(a);
+    ASQ_HIP_TRY(hipGetLastError());
+    fat_five_kernel<<<3 * nb, 256, 0, s>>>(a);
+    ASQ_HIP_TRY(hipGetLastError());
+    fat_link_kernel<<<a.nmu * nb64, 192, 0, s>>>(a);
+    ASQ_HIP_TRY(hipGetLastError());
+  }
+  a.mu0 = 0;
+  a.nmu = 4;
+  long_soa_kernel<<<nb64, 256, 0, s>>>(a);
   ASQ_HIP_TRY(hipGetLastError());
   return ASQ_OK;
 }

@@ -140,3 +140,58 @@ def test_tadpole_improved_construction(asq):
     x = asq.vec_from_device(res.x, 1, g.half, "f64")
     assert res.rc == 0
     assert oracle.true_residual(dims, fat, lng, mass, b[0], x[0]) <= 1e-10
+
+
+def _links_by(asq, dims, thin, u0, work_bytes):
+    """(rc, fat, long) of asqtad_build_links (work_bytes None) or asqtad_build_links_work."""
+    import ctypes
+
+    import torch
+
+    d4 = (ctypes.c_int * 4)(*dims)
+    fat, lng = torch.full_like(thin, float("nan")), torch.full_like(thin, float("nan"))
+    args = (d4, thin.data_ptr(), float(u0), fat.data_ptr(), lng.data_ptr())
+    if work_bytes is None:
+        rc = asq.asqtad_build_links(*args, asq.stream_ptr(None))
+    else:
+        work = torch.full((max(work_bytes, 256),), 255, dtype=torch.uint8, device="cuda")  # NaNs
+        rc = asq.asqtad_build_links_work(*args, work.data_ptr(), work_bytes, asq.stream_ptr(None))
+    torch.cuda.synchronize()
+    return rc, fat, lng
+
+
+# one block of 64 sites and a ragged one; extents of 4, where a two-site hop wraps to the
+# same site both ways; more sites than four directions at a time fit (one per launch there)
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (6, 4, 10, 6), (4, 14, 4, 6), (32, 32, 32, 34)])
+def test_links_workspace_matches_workspace_free(asq, dims):
+    """The staged form against the nested one on the same matrices.  Entries are sums of at most 86
+    products of up to seven matrices with entries of rms 0.4: both round each product by 1e-16 of its
+    size, so they agree to 1e-13 of the largest entry."""
+    import ctypes
+
+    import torch
+
+    print(f"links with a workspace dims={dims}", flush=True)
+    n = int(np.prod(dims)) * 4 * 18
+    thin = torch.randn(n, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(3)) * 0.3
+    need = asq.asqtad_links_workspace_bytes((ctypes.c_int * 4)(*dims))
+    rc0, f0, l0 = _links_by(asq, dims, thin, 0.9, None)
+    rc1, f1, l1 = _links_by(asq, dims, thin, 0.9, need)
+    assert rc0 == 0 and rc1 == 0
+    for a, b in ((f0, f1), (l0, l1)):
+        assert float((a - b).abs().max()) <= 1e-13 * float(a.abs().max())
+    assert _links_by(asq, dims, thin, 0.9, need - 256)[0] == asq.ASQ_ENOMEM
+
+
+def test_build_links_on_side_stream(asq):
+    """The binding's workspace belongs to the stream the kernels run on."""
+    import torch
+
+    dims = (6, 6, 4, 10)
+    thin = asq.links_to_device(synth.thin_links(dims, 0.4, seed=44).reshape(-1, 4, 3, 3))
+    want = asq.build_links(dims, thin, 0.9)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    got = asq.build_links(dims, thin, 0.9, stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
