@@ -601,43 +601,106 @@ __global__ void __launch_bounds__(256) long_link_kernel(const FattenArgs A) {
   for (int k = 0; k < 9; ++k) ql[k] = make_double2(L.e[k / 3][k % 3].re, L.e[k / 3][k % 3].im);
 }
 
-// Mean plaquette, first pass: one thread per site sums (1/3) Re tr over its six
-// planes in a fixed order, then one partial per block (block_sum's tree).
+// Mean plaquette, first pass: (1/3) Re tr of the six planes of each site, added in
+// a fixed order, then one partial per kBlock sites (block_sum's tree).
 // Re tr[U_mu(x) U_nu(x+mu) (U_nu(x) U_mu(x+nu))^dag] is the sum over the entries
 // of M1 conj(M2), so the last product is not formed.
+// Bound by reading the links (295 MB at 20^3 x 64).  A thread that read its sites'
+// canonical links itself touched 64 lines per load, each many times: 433 us.  Here
+// the block copies the links of kPlaqSites sites and of their four forward
+// neighbours to LDS in runs of 432 and 576 bytes, and a lane takes one plane of one
+// site from there.
+constexpr int kPlaqSites = 32;
+
 __global__ void __launch_bounds__(kBlock) plaquette_kernel(const FattenArgs A, double* partials) {
-  const long lex = (long)blockIdx.x * kBlock + threadIdx.x;
-  double v = 0;
-  if (lex < A.V) {
-    int x[4];
-    long r = lex;
-    x[0] = (int)(r % A.d[0]);
-    r /= A.d[0];
-    x[1] = (int)(r % A.d[1]);
-    r /= A.d[1];
-    x[2] = (int)(r % A.d[2]);
-    x[3] = (int)(r / A.d[2]);
-    for (int mu = 0; mu < 4; ++mu)
-      for (int nu = mu + 1; nu < 4; ++nu) {
-        int xm[4] = {x[0], x[1], x[2], x[3]}, xn[4] = {x[0], x[1], x[2], x[3]};
-        step(xm, mu, false, A.d);
-        step(xn, nu, false, A.d);
-        const M3 m1 = mul_nn(load_canonical(A, lex, mu), load_canonical(A, lex_of(A.d, xm), nu));
-        const M3 m2 = mul_nn(load_canonical(A, lex, nu), load_canonical(A, lex_of(A.d, xn), mu));
-        double t = 0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-          for (int b = 0; b < 3; ++b) {
-            t = fmaR(m1.e[a][b].re, m2.e[a][b].re, t);
-            t = fmaR(m1.e[a][b].im, m2.e[a][b].im, t);
-          }
-        v += t / 3.0;
-      }
-  }
+  __shared__ double2 own[kPlaqSites][37];       // U_mu(x), entry 9 mu + k (one spare: odd strides)
+  __shared__ double2 nbr[4][kPlaqSites][27];    // U_nu(x+mu), nu != mu in order
+  __shared__ double tr[6][kPlaqSites];
+  __shared__ double site[kBlock];               // with the others 78 KB: two blocks per CU
   __shared__ double sh[kBlock / 64];
+  __shared__ int fwd[4][kPlaqSites];            // x+mu, relative to the block's first site
+  const int tid = (int)threadIdx.x;
+  const int blk = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+  const long b0 = (long)blk * kBlock;
+  for (int c0 = 0; c0 < kBlock; c0 += kPlaqSites) {
+    const long s0 = b0 + c0;
+    const int n = (int)(A.V - s0 < kPlaqSites ? A.V - s0 : kPlaqSites);  // uniform over the block
+    if (n <= 0) break;
+    if (tid < 4 * kPlaqSites) {
+      const int mu = tid / kPlaqSites, j = tid % kPlaqSites;
+      long r = s0 + (j < n ? j : 0), stride = 1;
+      long q = r;
+      for (int a = 0; a < mu; ++a) {
+        stride *= A.d[a];
+        q /= A.d[a];
+      }
+      const bool last = q % A.d[mu] == A.d[mu] - 1;
+      fwd[mu][j] = (int)(r + (last ? stride * (1 - A.d[mu]) : stride) - b0);
+    }
+    __syncthreads();
+    // every load of the chunk is issued before the first store to LDS; threads
+    // past the end repeat the last entry
+    constexpr int kOwn = (kPlaqSites * 36 + kBlock - 1) / kBlock, kNbr = (kPlaqSites * 27 + kBlock - 1) / kBlock;
+    double2 vo[kOwn], vn[4][kNbr];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) vo[q] = A.thin[s0 * 36 + min(tid + q * kBlock, n * 36 - 1)];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+      for (int q = 0; q < kNbr; ++q) {
+        const int e = min(tid + q * kBlock, n * 27 - 1), k = e % 27;
+        vn[mu][q] = A.thin[(b0 + fwd[mu][e / 27]) * 36 + k + (k >= 9 * mu ? 9 : 0)];
+      }
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      const int e = min(tid + q * kBlock, n * 36 - 1);
+      own[e / 36][e % 36] = vo[q];
+    }
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+      for (int q = 0; q < kNbr; ++q) {
+        const int e = min(tid + q * kBlock, n * 27 - 1);
+        nbr[mu][e / 27][e % 27] = vn[mu][q];
+      }
+    __syncthreads();
+    const int pl = tid / kPlaqSites, j = tid % kPlaqSites;
+    if (pl < 6 && j < n) {
+      // planes (0,1) (0,2) (0,3) (1,2) (1,3) (2,3)
+      const int mu = pl < 3 ? 0 : (pl < 5 ? 1 : 2), nu = pl < 3 ? pl + 1 : (pl < 5 ? pl - 1 : 3);
+      auto get = [](const double2* q) {
+        M3 U;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+          U.e[k / 3][k % 3].re = q[k].x;
+          U.e[k / 3][k % 3].im = q[k].y;
+        }
+        return U;
+      };
+      const M3 m1 = mul_nn(get(&own[j][9 * mu]), get(&nbr[mu][j][9 * (nu - 1)]));  // nu > mu
+      const M3 m2 = mul_nn(get(&own[j][9 * nu]), get(&nbr[nu][j][9 * mu]));
+      double t = 0;
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          t = fmaR(m1.e[a][b].re, m2.e[a][b].re, t);
+          t = fmaR(m1.e[a][b].im, m2.e[a][b].im, t);
+        }
+      tr[pl][j] = t / 3.0;
+    }
+    __syncthreads();
+    if (tid < n) {  // tr is written again two barriers on
+      double v = 0;
+#pragma unroll
+      for (int p = 0; p < 6; ++p) v += tr[p][tid];
+      site[c0 + tid] = v;
+    }
+  }
+  __syncthreads();
+  const double v = b0 + tid < A.V ? site[tid] : 0.0;
   const double tot = block_sum(v, sh);
-  if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+  if (threadIdx.x == 0) partials[blk] = tot;
 }
 
 // Second pass: the partials in order, divided by the number of plaquettes.
