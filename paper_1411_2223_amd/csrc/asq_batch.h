@@ -16,14 +16,19 @@ inline bool ranges_overlap(const void* a, size_t na, const void* b, size_t nb) {
   return na && nb && pa < pb + nb && pb < pa + na;
 }
 
-// Widest batch whose D_eo launch forms alpha itself instead of a scalar launch
-// (its tiles are then at most kFoldAlphaMaxTile columns wide).
-constexpr int kFoldAlphaCols = kFoldAlphaMaxTile;
-// Most site blocks for which the launches fold alpha and beta in: every block
-// re-reads all nblk partials of its columns, which costs nblk^2 partial reads per
-// launch; up to 4 kBlock blocks a thread loads at most four of them, issued before
-// the hop loop (at 48^3 x 96, 20 736 blocks, a fold would re-read 6.9 GB).
+// Where the launches of an iteration fold the scalar steps in.  alpha: D_eo's
+// blocks re-sum 2 nblk partials per column of their tile, when the tuned tile is at
+// most kFoldAlphaMaxTile wide.  beta: each block of the direction update re-sums
+// nblk partials of its column, when that launch has at most kFoldMaxLaunch blocks
+// (more are bound by bandwidth: 20^3 x 64 with 4 columns, 4000 blocks, 63.2 ms without
+// and 63.5 with).
+// Each scalar launch costs about 6 us of an iteration: 8^4 with 4 columns 2.56 -> 2.11
+// ms a solve without them, 16^3 x 32 with 3 columns (768 update blocks) 16.4 -> 15.4.
+// Both up to kFoldMaxBlocks site blocks: nblk^2 partial reads per launch; up to
+// 4 kBlock blocks a thread loads at most four of them (at 48^3 x 96, 20 736 blocks, a
+// fold would re-read 6.9 GB).
 constexpr int kFoldMaxBlocks = 4 * kBlock;
+constexpr int kFoldMaxLaunch = 2048;
 
 struct Batch {
   const asq_gauge* g = nullptr;

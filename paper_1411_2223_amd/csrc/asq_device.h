@@ -18,6 +18,7 @@
 namespace asq {
 
 constexpr int kBlock = 256;  // sites per block and per reduction group (fixed: keeps sums batch-invariant)
+constexpr int kWaves = kBlock / 64;
 
 // n / d for 32-bit n and 2 <= d < 2^32 with a 64-bit magic multiplier:
 // m = floor(2^64 / d) + 1 gives floor(n*m / 2^64) = floor(n / d) exactly.

@@ -116,10 +116,12 @@ struct DslashArgs {
   void* x;              // UPDATE: solution accumulator (F32 segment sum, or the F64 x in FP64 mode)
   ColState* st;         // per-column a, alpha and masks (nullptr: all columns)
   int mask;
-  double* partials;     // [ncol][nblk] FP64 block partials (NORM, UPDATE, RESID)
+  double* partials;     // [ncol][nblk] FP64 block partials (NORM, UPDATE, RESID); [ncol][nblk][kWaves]
+                        // of the split form
   int nblk;
   const double* apa;    // UPDATE, when set: every block forms alpha = rr / (a sum(apa) + sum(apb))
   const double* apb;    // from the [ncol][nblk] partials of |p|^2 and |D_oe p|^2 itself
+  int apb_sub;          // 1, or kWaves: apb holds a partial per wave of sites (the split form's)
   int sgroup;           // block order: 0 site block by site block, else tile by tile in groups of sgroup
   double coeff_fat;     // 12-real tiers: fat / long coefficients re-applied in-kernel
   double coeff_long;
@@ -175,6 +177,14 @@ inline int sweep_chunk_of(int rtile) {
 // kMfmaBit | kMfmaTile | order << kOrderShift, 32 columns per block of sites.
 constexpr int kMfmaBit = 0x10000;
 constexpr int kMfmaTile = 32;
+// The split form (any tier, one column per block): blocks of 64 sites, a wave per
+// direction.  Its code is a run length without the sweep that runs belong to, which
+// no other variant uses.  Timed for launches of at most kSplitMaxBlocks site blocks
+// times columns (with more, every CU has a plain block already: 16^3 x 32, 256 blocks,
+// 13.1 us plain); chosen by the tuner only, the public variant call does not take it.
+constexpr int kSplitCode = 1 | (1 << kChunkShift);
+constexpr long kSplitMaxBlocks = 512;
+inline int partial_sub(int rtile) { return rtile == kSplitCode ? kWaves : 1; }
 inline int rtile_order(int rtile) { return (rtile >> kOrderShift) & 3; }
 inline int order_group(int order, int nblk) { return order == 0 ? 0 : (order == 1 ? 16 : (order == 2 ? 64 : nblk)); }
 // Whether the library builds launch variant rtile (for any link and vector tier).
@@ -187,7 +197,9 @@ inline int make_rtile(int cols, bool pipe, int order, bool global_sweep = false,
   return cols | (pipe ? kPipeBit : 0) | (stream ? kStreamBit : 0) | (lds ? kLdsBit : 0) | (order << kOrderShift) |
          (global_sweep ? kGlobalSweepBit | (chunk_code << kChunkShift) : 0);
 }
-// Widest column tile whose UPDATE launch may form alpha itself (DslashArgs::apa).
+// Widest column tile whose UPDATE launch may form alpha itself (DslashArgs::apa): its
+// partials are loaded before the hop loop.  (4-column tiles, which have no registers
+// for that and loaded them after it, made a 16^3 x 32 multi-shift solve 2 % slower.)
 constexpr int kFoldAlphaMaxTile = 2;
 
 // Tuned launch variant for a Dslash configuration.

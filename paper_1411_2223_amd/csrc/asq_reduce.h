@@ -128,19 +128,35 @@ __device__ inline void finalize_guess(ColState& S, double bb, double rr) {
   S.escalate = 0;
 }
 
+// Partial k of a column: the sum over its site block, or (SUB == kWaves) the sums of
+// the block's waves, added here in block_sum's order (a sum of squares plus a leading
+// zero is itself).
+template <int SUB>
+__device__ __forceinline__ double load_partial(const double* partials, int k) {
+  const double* q = partials + (size_t)k * SUB;
+  double v = q[0];
+#pragma unroll
+  for (int w = 1; w < SUB; ++w) v += q[w];
+  return v;
+}
+__device__ __forceinline__ double load_partial(const double* partials, int k, int sub) {
+  return sub == 1 ? load_partial<1>(partials, k) : load_partial<kWaves>(partials, k);
+}
+
 // This thread's share of a fixed-order sum of partials[0..n): elements
 // threadIdx.x, threadIdx.x + kBlock, ... added in increasing order.  Every
 // group of four loads, the last partial one included, is issued before its adds
 // (the same adds in the same order, so the same bits), so a sum of n partials
 // costs about n / (4 kBlock) memory round trips instead of n / kBlock.
+template <int SUB = 1>
 __device__ inline double strided_sum(const double* partials, int n) {
   double v = 0;
   for (int k = (int)threadIdx.x; k < n; k += 4 * kBlock) {
     const bool h1 = k + kBlock < n, h2 = k + 2 * kBlock < n, h3 = k + 3 * kBlock < n;
-    const double a = partials[k];
-    const double b = h1 ? partials[k + kBlock] : 0.0;
-    const double c = h2 ? partials[k + 2 * kBlock] : 0.0;
-    const double d = h3 ? partials[k + 3 * kBlock] : 0.0;
+    const double a = load_partial<SUB>(partials, k);
+    const double b = h1 ? load_partial<SUB>(partials, k + kBlock) : 0.0;
+    const double c = h2 ? load_partial<SUB>(partials, k + 2 * kBlock) : 0.0;
+    const double d = h3 ? load_partial<SUB>(partials, k + 3 * kBlock) : 0.0;
     v += a;
     if (h1) v += b;
     if (h2) v += c;

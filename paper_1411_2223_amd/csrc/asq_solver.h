@@ -22,12 +22,14 @@ struct VecArgs {
   // written to st_out (st itself is only read)
   ColState* st_out = nullptr;
   const double* beta_partials = nullptr;
+  int beta_sub = 1;  // partials per site block there (see partial_sub)
 };
 
 int launch_vec_kernel(int which, int pt, int rt, const VecArgs& a, int ncol, hipStream_t s);
 // x[0..n) = hashed values in [-1, 1) (trial data for the autotuner).
 int fill_trial_values(double* x, size_t n, hipStream_t s);
+// sub: partials per site block in pb (partial_sub of the Dslash that wrote them; pa has one).
 int launch_reduce(int op, ColState* st, const double* pa, const double* pb, int nblk, int ncol, hipStream_t s,
-                  ColState* dst = nullptr);
+                  int sub = 1, ColState* dst = nullptr);
 
 }  // namespace asq

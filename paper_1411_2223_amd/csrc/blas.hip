@@ -71,12 +71,12 @@ __global__ void __launch_bounds__(kBlock) guess_kernel(const VecArgs A) {
 
 // p_new = r + beta p into the buffer that is not current; partials of |p_new|^2
 // (as stored), which give <p, A p> = a |p|^2 + |D_oe p|^2 without a dot with A p.
-// With A.st_out set, the kernel first does the scalar kernel's OP_BETA step
-// for the previous iteration: every block sums the |r|^2 partials in the same
+// FOLD > 0 (A.st_out set): the kernel first does the scalar kernel's OP_BETA step
+// for the previous iteration, from FOLD partials per site block: every block sums the |r|^2 partials in the same
 // order and tree and finalises a private copy of the state, so all blocks take
 // the same decisions; block 0 writes that copy to st_out.  The state is read
 // from st only, so no block can see another block's write.
-template <class PT, class RT>
+template <class PT, class RT, int FOLD>
 __global__ void __launch_bounds__(kBlock) update_p_kernel(const VecArgs A) {
   const int c = blockIdx.y, sblk = blockIdx.x;
   using pr = typename PT::real;
@@ -88,7 +88,7 @@ __global__ void __launch_bounds__(kBlock) update_p_kernel(const VecArgs A) {
   // checked against the finalised state below.
   const ColState& G = A.st[c];
   const bool was_on = state_on(G, MASK_ACTIVE);  // a column that is off stays off
-  const int pbuf_guess = (A.st_out && was_on) ? G.pbuf ^ 1 : G.pbuf;
+  const int pbuf_guess = (FOLD > 0 && was_on) ? G.pbuf ^ 1 : G.pbuf;
   Vec3<pr> r, p;
   if (was_on && i < half) {
     r = convert<pr>(RT::load(A.r, half, c, i));
@@ -97,8 +97,8 @@ __global__ void __launch_bounds__(kBlock) update_p_kernel(const VecArgs A) {
   // the block's copy of the state lives in LDS (a per-thread copy would be
   // placed in LDS by the compiler too, once per thread)
   __shared__ ColState S;
-  if (A.st_out) {
-    const double s = strided_sum(A.beta_partials + (size_t)c * A.nblk, A.nblk);
+  if constexpr (FOLD > 0) {
+    const double s = strided_sum<FOLD>(A.beta_partials + (size_t)c * A.nblk * FOLD, A.nblk);
     __shared__ double shb[kBlock / 64];
     const double tot = block_sum(s, shb);  // valid in thread 0
     if (threadIdx.x == 0) {
@@ -154,11 +154,13 @@ __global__ void __launch_bounds__(kBlock) flush_x_kernel(const VecArgs A) {
 // loaded before the column state so that the two latencies overlap.
 // With dst set (OP_BETA only), the state is read from st and the finalised
 // copy written to dst, whether or not the column takes part.
+// SUB: partials per site block in pb.
+template <int SUB>
 __global__ void __launch_bounds__(kBlock) reduce_kernel(ColState* st, const double* pa, const double* pb, int nblk,
                                                         int op, ColState* dst) {
   const int c = blockIdx.x;
   const bool two = op == OP_ALPHA || op == OP_INIT_GUESS;
-  const double vb = strided_sum(pb + (size_t)c * nblk, nblk);
+  const double vb = strided_sum<SUB>(pb + (size_t)c * nblk * SUB, nblk);
   const double va = two ? strided_sum(pa + (size_t)c * nblk, nblk) : 0.0;
   const int mask = (op == OP_ALPHA || op == OP_BETA) ? MASK_ACTIVE : (op == OP_RU ? MASK_RELIABLE : MASK_ALL);
   if (dst) {
@@ -258,7 +260,9 @@ int launch_vec(int which, const VecArgs& a, int ncol, hipStream_t s) {
   if (which == VK_INIT) {
     init_kernel<PT, RT><<<grid, kBlock, 0, s>>>(a);
   } else if (which == VK_P) {
-    update_p_kernel<PT, RT><<<grid, kBlock, 0, s>>>(a);
+    if (!a.st_out) update_p_kernel<PT, RT, 0><<<grid, kBlock, 0, s>>>(a);
+    else if (a.beta_sub == 1) update_p_kernel<PT, RT, 1><<<grid, kBlock, 0, s>>>(a);
+    else update_p_kernel<PT, RT, kWaves><<<grid, kBlock, 0, s>>>(a);
   } else if (which == VK_GUESS) {
     guess_kernel<PT, RT><<<grid, kBlock, 0, s>>>(a);
   } else if (which == VK_FLUSH) {
@@ -300,10 +304,11 @@ int launch_vec_kernel(int which, int pt, int rt, const VecArgs& a, int ncol, hip
 }
 
 int launch_reduce(int op, ColState* st, const double* pa, const double* pb, int nblk, int ncol, hipStream_t s,
-                  ColState* dst) {
+                  int sub, ColState* dst) {
   if ((op == OP_ALPHA || op == OP_INIT_GUESS) && !pa) return ASQ_EINVAL;
   if (dst && (op != OP_BETA || dst == st)) return ASQ_EINVAL;
-  reduce_kernel<<<(unsigned)ncol, kBlock, 0, s>>>(st, pa, pb, nblk, op, dst);
+  if (sub == 1) reduce_kernel<1><<<(unsigned)ncol, kBlock, 0, s>>>(st, pa, pb, nblk, op, dst);
+  else reduce_kernel<kWaves><<<(unsigned)ncol, kBlock, 0, s>>>(st, pa, pb, nblk, op, dst);
   return hipGetLastError() == hipSuccess ? ASQ_OK : ASQ_EHIP;
 }
 

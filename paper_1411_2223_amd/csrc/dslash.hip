@@ -11,6 +11,7 @@ bool variant_built(int link_kind, int in_kind, int rtile) {
     if ((rtile & ~(kMfmaBit | 0xff | (3 << kOrderShift))) != 0) return false;
     return link_kind == LINK_F32_R18 && in_kind == VEC_F16 && cols == kMfmaTile;
   }
+  if (rtile == kSplitCode) return true;
   if ((rtile & ~(0xff | kPipeBit | kStreamBit | kLdsBit | (3 << kOrderShift) | kGlobalSweepBit | (3 << kChunkShift))) !=
       0)
     return false;

@@ -334,13 +334,13 @@ __global__ void __launch_bounds__(kBlock) dslash_kernel(const DslashArgs A) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const double* pa = A.apa + (size_t)(c0 + r) * A.nblk;
-        const double* pb = A.apb + (size_t)(c0 + r) * A.nblk;
+        const double* pb = A.apb + (size_t)(c0 + r) * A.nblk * A.apb_sub;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int k = tid + q * kBlock;
           const bool in = on[r] && k < A.nblk;
           qa[r][q] = in ? pa[k] : 0.0;
-          qb[r][q] = in ? pb[k] : 0.0;
+          qb[r][q] = in ? load_partial(pb, k, A.apb_sub) : 0.0;
         }
       }
     }
@@ -497,6 +497,241 @@ __global__ void __launch_bounds__(kBlock) dslash_kernel(const DslashArgs A) {
   }
 }
 
+// Split form for launches of few site blocks (one column per block).  A block of the
+// plain form reads 300 KB (FP32) through one CU, and 8^3 x 8 has 8 of them: 7.8 us of
+// waiting for what a CU can have in flight.  Here a block is 64 sites, a wave per
+// direction, so that lattice runs on 32 CUs and a wave waits for one round of loads
+// instead of a chain of eight.  Wave 0 adds the products of the others, passed
+// through LDS, to its own in the order of the plain loop: the same result bit for bit.
+// The epilogues leave one partial per wave of sites (kWaves per site block); their
+// consumers add the four in block_sum's order (load_partial).
+// Neighbour h steps along mu, and the scale of a term, for a direction known only at
+// run time (uniform over the wave).
+__device__ __forceinline__ int neighbour_of(const Geom& g, int i, const Site& s, int mu, int h) {
+  if (mu == 0) return neighbour<0>(g, i, s, h);
+  const int c = mu == 1 ? s.y : (mu == 2 ? s.z : s.t);
+  const int L = mu == 1 ? g.Y : (mu == 2 ? g.Z : g.T);
+  const int st = mu == 1 ? g.sY : (mu == 2 ? g.sZ : g.sT);
+  return i + (wrap(c + h, L) - c) * st;
+}
+
+// coefficient * eta * time-boundary sign (12-real tiers; 1 for folded links) of the
+// term of direction mu and hop kind KIND (+1, -1, +3, -3)
+template <class Link, class InT, int KIND>
+__device__ __forceinline__ typename InT::real scale_of(const DslashArgs& A, const Site& s, int mu) {
+  using real = typename InT::real;
+  real sc = 1;
+  if constexpr (!Link::folded) {
+    const int n = (mu > 0 ? s.x : 0) + (mu > 1 ? s.y : 0) + (mu > 2 ? s.z : 0);
+    sc = (real)((n & 1) ? -1 : 1) * (real)(KIND < 2 ? A.coeff_fat : A.coeff_long);
+    const int t = s.t, Tn = A.g.T;
+    const bool flip = KIND == 0 ? (t == Tn - 1) : KIND == 1 ? (t == 0) : KIND == 2 ? (t >= Tn - 3) : (t < 3);
+    if (mu == 3 && flip) sc = -sc;
+  }
+  return sc;
+}
+
+// A term in two steps, the product u (and its scale) and its addition to acc, with
+// the arithmetic of term().
+template <class Link, class InT>
+constexpr bool kScaled = InT::kind == VEC_F16 || !Link::folded;
+
+template <class Link, class InT, bool ADJ>
+__device__ __forceinline__ Vec3<typename InT::real> term_product(const typename InT::raw& w,
+                                                                 const Mat3<typename InT::real>& U,
+                                                                 typename InT::real scale, bool neg,
+                                                                 typename InT::real& sc) {
+  if constexpr (InT::kind == VEC_F16) {
+    const float nu = __uint_as_float(w.w);
+    const Vec3<float> h = VecF16::halves(w);
+    sc = Link::folded ? nu : nu * scale;
+    if (neg) sc = -sc;
+    return ADJ ? mul_adj(U, h) : mul(U, h);
+  } else {
+    sc = neg ? -scale : scale;
+    return ADJ ? mul_adj(U, w) : mul(U, w);
+  }
+}
+
+template <class Link, class InT>
+__device__ __forceinline__ void term_add(const Vec3<typename InT::real>& u, typename InT::real sc, bool neg,
+                                         Vec3<typename InT::real>& acc) {
+  if constexpr (kScaled<Link, InT>) {
+    axpy3(acc, sc, u);
+  } else {
+    if (neg) sub3(acc, u);
+    else add3(acc, u);
+  }
+}
+
+constexpr int kSplitSites = 64;
+template <class Link, class InT>
+constexpr int kSplitWords = kScaled<Link, InT> ? 7 : 6;  // reals of a product and its scale
+
+template <class Link, class InT, int KIND>
+__device__ __forceinline__ void split_load(const DslashArgs& A, int i, const Site& s, int mu, int c, const void* in,
+                                           Stage<Link, InT, 1>& st) {
+  constexpr bool back = (KIND & 1) != 0;
+  const int j = neighbour_of(A.g, i, s, mu, KIND == 0 ? 1 : (KIND == 1 ? -1 : (KIND == 2 ? 3 : -3)));
+  const int p = A.out_parity, half = A.g.half;
+  // the links of such lattices stay in the caches: ordinary loads in every tier
+  st.U = Link::load(A.links, half, back ? 1 - p : p, (KIND < 2 ? 0 : 4) + mu, back ? j : i);
+  st.w[0] = fetch<InT>(in, half, A.ncol, c, j);
+}
+
+template <class Link, class InT, int KIND>
+__device__ __forceinline__ Vec3<typename InT::real> split_product(const DslashArgs& A, const Site& s, int mu,
+                                                                  const Stage<Link, InT, 1>& st,
+                                                                  typename InT::real& sc) {
+  constexpr bool back = (KIND & 1) != 0;
+  return term_product<Link, InT, back>(st.w[0], st.U, scale_of<Link, InT, KIND>(A, s, mu), back, sc);
+}
+
+// The epilogue at one site (the arithmetic of dslash_kernel's): the site's term of
+// the reduction.
+template <class InT, class OutT, int EPI>
+__device__ __forceinline__ double split_epilogue(const DslashArgs& A, int c, int i, const Vec3<typename InT::real>& acc,
+                                                 double alpha) {
+  using real = typename InT::real;
+  const int half = A.g.half;
+  if constexpr (EPI == EPI_PLAIN) {
+    store_any<OutT>(A.out, half, A.ncol, c, i, convert<typename OutT::real>(acc));
+    return 0;
+  } else if constexpr (EPI == EPI_NORM) {
+    return norm2_d(OutT::store(A.out, half, c, i, convert<typename OutT::real>(acc)));
+  } else if constexpr (EPI == EPI_UPDATE) {
+    using rr = typename OutT::real;
+    using xv = typename std::conditional<InT::kind == VEC_F64, VecF64, VecF32>::type;
+    using xr = typename xv::real;
+    const Vec3<real> y = InT::load(A.y_sel ? pick_new(A, A.y, A.y_alt, c) : A.y, half, c, i);
+    const real a = (real)A.st[c].a;
+    const rr ar = (rr)alpha;
+    const xr al = (xr)alpha;
+    Vec3<rr> rv = OutT::load(A.r, half, c, i);
+    Vec3<xr> x = xv::load(A.x, half, c, i);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      rv.c[k].re = fmaR(-ar, (rr)fmaR(a, y.c[k].re, -acc.c[k].re), rv.c[k].re);
+      rv.c[k].im = fmaR(-ar, (rr)fmaR(a, y.c[k].im, -acc.c[k].im), rv.c[k].im);
+      x.c[k].re = fmaR(al, (xr)y.c[k].re, x.c[k].re);
+      x.c[k].im = fmaR(al, (xr)y.c[k].im, x.c[k].im);
+    }
+    xv::store(A.x, half, c, i, x);
+    return norm2_d(OutT::store(A.r, half, c, i, rv));
+  } else {
+    const double a = A.st[c].a;
+    const Vec3<double> y = VecF64::load(A.y, half, c, i);
+    const Vec3<double> b = VecF64::load(A.b, half, c, i);
+    Vec3<double> o;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      o.c[k].re = __builtin_fma(-a, y.c[k].re, b.c[k].re) + (double)acc.c[k].re;
+      o.c[k].im = __builtin_fma(-a, y.c[k].im, b.c[k].im) + (double)acc.c[k].im;
+    }
+    OutT::store(A.out, half, c, i, convert<typename OutT::real>(o));
+    return norm2_d(o);
+  }
+}
+
+template <class Link, class InT, class OutT, int EPI>
+__global__ void __launch_bounds__(4 * kSplitSites) dslash_split_kernel(const DslashArgs A) {
+  using real = typename InT::real;
+  constexpr int W = kSplitWords<Link, InT>;
+  __shared__ real prod[12][W][kSplitSites];
+  int lin = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+  if (A.reverse) lin = (int)gridDim.x - 1 - lin;
+  const int c = lin % A.ncol, sub = lin / A.ncol;  // sub: group of 64 sites
+  const int mu = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSplitSites);
+  const int lane = (int)threadIdx.x % kSplitSites;
+  const bool lead = mu == 0;
+  if (!col_on(A, c)) return;  // uniform over the block
+  const void* in = A.in_sel ? pick_new(A, A.in, A.in_alt, c) : A.in;
+  const int i = sub * kSplitSites + lane;
+  const bool valid = i < A.g.half;
+  // the partials that alpha is formed from, as in the plain form
+  [[maybe_unused]] double pp = 0, tt = 0;
+  if constexpr (EPI == EPI_UPDATE) {
+    if (A.apa) {
+      pp = strided_sum(A.apa + (size_t)c * A.nblk, A.nblk);
+      const double* pb = A.apb + (size_t)c * A.nblk * A.apb_sub;
+      tt = A.apb_sub == 1 ? strided_sum(pb, A.nblk) : strided_sum<kWaves>(pb, A.nblk);
+    }
+  }
+  Vec3<real> u[4];
+  real sc[4];
+  if (valid) {
+    const Site s = decode(A.g, i, A.out_parity);
+    Stage<Link, InT, 1> st[4];
+    split_load<Link, InT, 0>(A, i, s, mu, c, in, st[0]);
+    split_load<Link, InT, 1>(A, i, s, mu, c, in, st[1]);
+    split_load<Link, InT, 2>(A, i, s, mu, c, in, st[2]);
+    split_load<Link, InT, 3>(A, i, s, mu, c, in, st[3]);
+    u[0] = split_product<Link, InT, 0>(A, s, mu, st[0], sc[0]);
+    u[1] = split_product<Link, InT, 1>(A, s, mu, st[1], sc[1]);
+    u[2] = split_product<Link, InT, 2>(A, s, mu, st[2], sc[2]);
+    u[3] = split_product<Link, InT, 3>(A, s, mu, st[3], sc[3]);
+    if (!lead) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        real(*q)[kSplitSites] = prod[(mu - 1) * 4 + k];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          q[2 * a][lane] = u[k].c[a].re;
+          q[2 * a + 1][lane] = u[k].c[a].im;
+        }
+        if constexpr (W == 7) q[6][lane] = sc[k];
+      }
+    }
+  }
+  __syncthreads();
+  [[maybe_unused]] double alpha = 0;
+  if constexpr (EPI == EPI_UPDATE) {
+    alpha = A.st[c].alpha;
+    if (A.apa) {
+      __shared__ double sa[2 * (kWaves + 1)];
+      block_sum2_all(pp, tt, sa);
+      if (!fold_alpha(A, c, sub, pp, tt, alpha)) return;  // uniform over the block
+    }
+  }
+  if (!lead) return;
+  Vec3<real> acc;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) acc.c[a].re = acc.c[a].im = 0;
+  double d = 0;
+  if (valid) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) term_add<Link, InT>(u[k], sc[k], (k & 1) != 0, acc);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      Vec3<real> v;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        v.c[a].re = prod[k][2 * a][lane];
+        v.c[a].im = prod[k][2 * a + 1][lane];
+      }
+      real f = 0;
+      if constexpr (W == 7) f = prod[k][6][lane];
+      term_add<Link, InT>(v, f, (k & 1) != 0, acc);
+    }
+    d = split_epilogue<InT, OutT, EPI>(A, c, i, acc, alpha);
+  }
+  if constexpr (EPI != EPI_PLAIN) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o, 64);
+    if (lane == 0) A.partials[(size_t)c * A.nblk * kWaves + sub] = d;
+  }
+}
+
+template <class Link, class InT, class OutT, int EPI>
+int go_split(const DslashArgs& a, hipStream_t s) {
+  if (a.apa && a.nblk > 4 * kBlock) return ASQ_EINVAL;
+  const long nb = (long)a.nblk * kWaves * a.ncol;
+  if (nb <= 0) return ASQ_OK;
+  if (nb >= (1L << 31)) return ASQ_EINVAL;
+  dslash_split_kernel<Link, InT, OutT, EPI><<<(unsigned)nb, 4 * kSplitSites, 0, s>>>(a);
+  return hipGetLastError() == hipSuccess ? ASQ_OK : ASQ_EHIP;
+}
+
 template <class Link, class InT, class OutT, int R, int EPI, bool PIPE, bool LDS = false>
 int go(const DslashArgs& a0, int order, int sweep_chunk, hipStream_t s) {
   // alpha is formed in-kernel only by narrow tiles, from at most 4 kBlock partials
@@ -521,6 +756,7 @@ int go(const DslashArgs& a0, int order, int sweep_chunk, hipStream_t s) {
 // thread, the software-pipelined hop loop, the block order.
 template <class Link, class InT, class OutT, int EPI>
 int pick_r(int rtile, const DslashArgs& a, hipStream_t s) {
+  if (rtile == kSplitCode) return go_split<Link, InT, OutT, EPI>(a, s);
   const bool pipe = (rtile & kPipeBit) != 0;
   const int ord = rtile_order(rtile);
   const int gs = sweep_chunk_of(rtile);

@@ -68,7 +68,8 @@ size_t batch_bytes(const asq_gauge* g, int ncol, int mode, bool with_bx) {
   const int pt = mode_pt(mode), rt = mode_rt(mode);
   size_t n = 0;
   n += 2 * align_up((size_t)ncol * sizeof(ColState), 256);  // states (two copies)
-  n += 3 * align_up((size_t)ncol * g->nblk * sizeof(double), 256);  // partials (three sets)
+  n += align_up((size_t)ncol * g->nblk * sizeof(double), 256);                // partials of |p|^2
+  n += 2 * align_up((size_t)ncol * g->nblk * kWaves * sizeof(double), 256);  // and of a Dslash (two sets)
   n += align_up((size_t)ncol * half * vec_site_bytes(rt), 256);      // r
   n += 3 * align_up((size_t)ncol * half * vec_site_bytes(pt), 256);  // p, p_alt, t
   if (mode != ASQ_MODE_F64) n += align_up((size_t)ncol * half * 48, 256);  // t64
@@ -113,9 +114,9 @@ int batch_carve(Batch& B, const asq_gauge* g, int ncol, int mode, void* work, si
   B.pt = pt;
   B.rt = rt;
   B.st = (ColState*)take((size_t)ncol * sizeof(ColState));
-  B.partials = (double*)take((size_t)ncol * g->nblk * sizeof(double));
+  B.partials = (double*)take((size_t)ncol * g->nblk * kWaves * sizeof(double));
   B.partials_p = (double*)take((size_t)ncol * g->nblk * sizeof(double));
-  B.partials_t = (double*)take((size_t)ncol * g->nblk * sizeof(double));
+  B.partials_t = (double*)take((size_t)ncol * g->nblk * kWaves * sizeof(double));
   B.r = take((size_t)ncol * half * vec_site_bytes(rt));
   B.p = take((size_t)ncol * half * vec_site_bytes(pt));
   B.p_alt = take((size_t)ncol * half * vec_site_bytes(pt));
@@ -132,12 +133,6 @@ int batch_carve(Batch& B, const asq_gauge* g, int ncol, int mode, void* work, si
   B.st2 = (ColState*)take((size_t)ncol * sizeof(ColState));
   B.link = sloppy_link(g, mode);
   B.sweep = env_flag("ASQ_SWEEP", true);
-  // Each D_eo block re-sums 2 x nblk partials per column of its tile, which is
-  // cheap next to the Dslash only for narrow batches on lattices of at most
-  // kFoldMaxBlocks site blocks.
-  B.fold_alpha = ncol <= kFoldAlphaCols && g->nblk <= kFoldMaxBlocks && env_flag("ASQ_FOLD_ALPHA", true);
-  // Likewise each direction-update block re-sums nblk partials of its column.
-  B.fold_beta = ncol <= kFoldAlphaCols && g->nblk <= kFoldMaxBlocks && env_flag("ASQ_FOLD_BETA", true);
   batch_pick_tiles(B);
   return ASQ_OK;
 }
@@ -148,6 +143,10 @@ void batch_pick_tiles(Batch& B) {
   B.rt_sloppy_update = tuned_rtile(g, B.link, B.pt, B.rt, EPI_UPDATE, B.ncol);
   B.rt64_plain = tuned_rtile(g, LINK_F64_R18, VEC_F64, VEC_F64, EPI_PLAIN, B.ncol);
   B.rt64_resid = tuned_rtile(g, LINK_F64_R18, VEC_F64, B.rt, EPI_RESID, B.ncol);
+  const bool few = g->nblk <= kFoldMaxBlocks;
+  B.fold_alpha = few && !(B.rt_sloppy_update & kMfmaBit) && (B.rt_sloppy_update & 0xff) <= kFoldAlphaMaxTile &&
+                 env_flag("ASQ_FOLD_ALPHA", true);
+  B.fold_beta = few && (long)g->nblk * B.ncol <= kFoldMaxLaunch && env_flag("ASQ_FOLD_BETA", true);
 }
 
 // Autotune the batch's Dslash launches on its own buffers (p -> t, x -> t64),
@@ -234,7 +233,7 @@ int enqueue_init_guess(const Batch& B, hipStream_t s) {
   d2.b = B.b;
   rc = launch_dslash(LINK_F64_R18, VEC_F64, B.rt, EPI_RESID, B.rt64_resid, d2, s);
   if (rc) return rc;
-  return launch_reduce(OP_INIT_GUESS, B.st, B.partials_p, B.partials, g->nblk, B.ncol, s);
+  return launch_reduce(OP_INIT_GUESS, B.st, B.partials_p, B.partials, g->nblk, B.ncol, s, partial_sub(B.rt64_resid));
 }
 
 // One CG iteration.  The direction update reads the column states from `in`;
@@ -254,6 +253,7 @@ int enqueue_iteration(const Batch& B, hipStream_t s, ColState* in, ColState* out
   if (in != out) {
     v.st_out = out;
     v.beta_partials = B.partials;
+    v.beta_sub = partial_sub(B.rt_sloppy_update);
   }
   int rc = launch_vec_kernel(VK_P, B.pt, B.rt, v, B.ncol, s);
   if (rc) return rc;
@@ -268,7 +268,7 @@ int enqueue_iteration(const Batch& B, hipStream_t s, ColState* in, ColState* out
   if (rc) return rc;
   // alpha = rr / (a |p|^2 + |t|^2): a scalar launch, or inside D_eo
   if (!B.fold_alpha) {
-    rc = launch_reduce(OP_ALPHA, out, B.partials_p, B.partials_t, g->nblk, B.ncol, s);
+    rc = launch_reduce(OP_ALPHA, out, B.partials_p, B.partials_t, g->nblk, B.ncol, s, partial_sub(B.rt_sloppy_norm));
     if (rc) return rc;
   }
   // Ap = a p - D_eo t; r -= alpha Ap; x += alpha p; partials of |r|^2 (backward sweep)
@@ -277,6 +277,7 @@ int enqueue_iteration(const Batch& B, hipStream_t s, ColState* in, ColState* out
   if (B.fold_alpha) {
     d2.apa = B.partials_p;
     d2.apb = B.partials_t;
+    d2.apb_sub = partial_sub(B.rt_sloppy_norm);
   }
   d2.links = L;
   d2.y = B.p;
@@ -289,7 +290,7 @@ int enqueue_iteration(const Batch& B, hipStream_t s, ColState* in, ColState* out
   if (rc) return rc;
   if (defer_beta) return ASQ_OK;
   // beta, triggers, p buffer swap
-  return launch_reduce(OP_BETA, out, nullptr, B.partials, g->nblk, B.ncol, s);
+  return launch_reduce(OP_BETA, out, nullptr, B.partials, g->nblk, B.ncol, s, partial_sub(B.rt_sloppy_update));
 }
 
 int enqueue_iteration(const Batch& B, hipStream_t s) { return enqueue_iteration(B, s, B.st, B.st, false); }
@@ -317,7 +318,7 @@ int enqueue_reliable(const Batch& B, int mask, int op, hipStream_t s) {
   d2.reverse = B.sweep ? 1 : 0;
   rc = launch_dslash(LINK_F64_R18, VEC_F64, B.rt, EPI_RESID, B.rt64_resid, d2, s);
   if (rc) return rc;
-  return launch_reduce(op, B.st, nullptr, B.partials, g->nblk, B.ncol, s);
+  return launch_reduce(op, B.st, nullptr, B.partials, g->nblk, B.ncol, s, partial_sub(B.rt64_resid));
 }
 
 // `iters` iterations, then the reliable update of the columns that asked for
@@ -334,8 +335,8 @@ int enqueue_block(const Batch& B, int iters, hipStream_t s) {
     cur = next;
   }
   if (B.fold_beta && iters > 0) {
-    const int rc = cur == B.st ? launch_reduce(OP_BETA, B.st, nullptr, B.partials, B.g->nblk, B.ncol, s)
-                               : launch_reduce(OP_BETA, cur, nullptr, B.partials, B.g->nblk, B.ncol, s, B.st);
+    const int rc = launch_reduce(OP_BETA, cur, nullptr, B.partials, B.g->nblk, B.ncol, s,
+                                 partial_sub(B.rt_sloppy_update), cur == B.st ? nullptr : B.st);
     if (rc) return rc;
   }
   return enqueue_reliable(B, MASK_RELIABLE, OP_RU, s);
@@ -715,6 +716,10 @@ extern "C" int asqtad_dslash_eo_variant(const asq_gauge* g, int out_parity, int 
   const bool native = (variant & ASQ_VARIANT_NATIVE) != 0;
   int v = variant & ~ASQ_VARIANT_NATIVE;
   if (native && v == 0) v = -1;  // the tuned variant on native vectors
+  if (v == kSplitCode) {
+    set_last_error("asqtad_dslash_eo_variant: unknown variant code");
+    return ASQ_EINVAL;
+  }
   if (!native && (v & kMfmaBit)) {
     set_last_error("asqtad_dslash_eo_variant: the matrix-core form takes the native layout only");
     return ASQ_EINVAL;

@@ -91,8 +91,7 @@ int tuned_rtile(const asq_gauge* g, int link, int in, int out, int epi, int ncol
   const int fv = forced_variant(link, in);
   // a forced tile wider than the batch, or whose LDS window does not fit this
   // lattice, is ignored, except the matrix-core form, which masks its idle
-  // columns; that form takes alpha from the column state, so it is not forced
-  // where the update launch forms alpha itself
+  // columns; that form is for many columns and not forced on one or two
   if (fv >= 0 && !(fv & kMfmaBit) && (fv & 0xff) <= (ncol > 1 ? ncol : 1) && variant_fits(g->geom, in, fv)) return fv;
   if (fv >= 0 && (fv & kMfmaBit) && ncol > kFoldAlphaMaxTile) return fv;
   std::lock_guard<std::mutex> lk(g_mu);
@@ -177,6 +176,8 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
       for (size_t q = 0; q < n; ++q)
         if (variant_built(link, in, cands[q] | kLdsBit)) cands.push_back(cands[q] | kLdsBit);
     }
+    // launches of few blocks: the split form
+    if ((long)g->nblk * ncol <= kSplitMaxBlocks) cands.push_back(kSplitCode);
     // The solver runs D_oe forwards and D_eo backwards, so each sweep starts on
     // the links and vectors the previous one left in the memory-side cache; the
     // candidates are timed in that pattern (pairs of launches), best of two.
@@ -204,7 +205,7 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
         if (ok && t < ms) ms = t;
       }
       if (!ok) continue;
-      if (log_enabled()) fprintf(stderr, "[asq] tune %s R=%d %.3f ms\n", kp.c_str(), r, ms / 4);
+      if (log_enabled()) fprintf(stderr, "[asq] tune %s R=%d %.4f ms\n", kp.c_str(), r, ms / 4);
       if (ms < best_ms) {
         best_ms = ms;
         best = r;

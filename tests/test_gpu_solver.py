@@ -545,3 +545,51 @@ def test_stalled_columns_escalate(asq, mode, monkeypatch):
     monkeypatch.delenv("ASQ_STALL_DROP")
     x2, r2 = _solve(asq, g, masses, b, mode)
     assert r2.rc == 0 and all(s["escalations"] == 0 and s["final_mode"] == asq.MODES[mode] for s in r2.stats)
+
+
+# (4,4,4,4): half a site block; (6,4,10,6): 720 even sites, a ragged block and a ragged wave;
+# (4,6,8,16): whole blocks.  The FP32 field also serves as the FP64-links-rounded tier.
+@pytest.mark.parametrize("dims,n", [((4, 4, 4, 4), 1), ((6, 4, 10, 6), 3), ((4, 6, 8, 16), 5)])
+@pytest.mark.parametrize("precs,recon,modes", [(("f64", "f32"), 18, ("f64", "mixed32", "mixed16")),
+                                               (("f64", "f32", "f16"), 12, ("mixed32", "mixed16")),
+                                               (("f64",), 18, ("mixed32", "mixed16"))])
+def test_split_form_is_bitwise_the_plain_form(asq, monkeypatch, dims, n, precs, recon, modes):
+    """The launch form for few site blocks (64-site blocks, a wave per direction, a partial per
+    wave) gives the bits of the plain form: operator in every tier on both layouts and parities,
+    and whole solves with every epilogue, with alpha and beta folded in and by scalar launches."""
+    monkeypatch.setenv("ASQ_TUNE", "0")
+    split = str(1 | 1 << 10)
+    fat, lng = synth.make_gauge(dims, 0.3, 77)
+    g = asq.Gauge(dims, fat, lng, precs=precs, recon=recon)
+    b = asq.vec_to_device(synth.make_sources(dims, n, 78))
+    for prec in ("f64", "f32", "f16"):
+        v = b if prec == "f64" else asq.vec_convert(b, n * g.half, "f64", prec)
+        for parity, variant in ((0, None), (1, None), (1, asq.ASQ_VARIANT_NATIVE)):
+            print(f"split operator {dims} {precs} {prec} parity {parity} variant {variant}", flush=True)
+            monkeypatch.delenv("ASQ_VARIANT", raising=False)
+            want = g.dslash(parity, v, prec, n, variant=variant)
+            monkeypatch.setenv("ASQ_VARIANT", split)
+            got = g.dslash(parity, v, prec, n, variant=variant)
+            assert got.cpu().numpy().tobytes() == want.cpu().numpy().tobytes()
+    masses = [0.1 + 0.02 * k for k in range(n)]
+    for mode in modes:
+        print(f"split solve {dims} {precs} {mode} n={n}", flush=True)
+        monkeypatch.delenv("ASQ_VARIANT", raising=False)
+        monkeypatch.setenv("ASQ_FOLD_ALPHA", "0")
+        monkeypatch.setenv("ASQ_FOLD_BETA", "0")
+        want = g.solve(masses, b, mode=mode)
+        for fold in ("0", "1"):
+            monkeypatch.setenv("ASQ_FOLD_ALPHA", fold)
+            monkeypatch.setenv("ASQ_FOLD_BETA", fold)
+            for variant in (split, None):
+                if variant:
+                    monkeypatch.setenv("ASQ_VARIANT", variant)
+                else:
+                    monkeypatch.delenv("ASQ_VARIANT", raising=False)
+                got = g.solve(masses, b, mode=mode)
+                assert got.x.cpu().numpy().tobytes() == want.x.cpu().numpy().tobytes()
+                for s, t in zip(got.stats, want.stats):
+                    assert {k: s[k] for k in ("iters", "reliable_updates", "converged", "true_resid")} == {
+                        k: t[k] for k in ("iters", "reliable_updates", "converged", "true_resid")}
+    with pytest.raises(asq.AsqError):  # the tuner's own choice: not a code of the variant call
+        g.dslash(1, b, "f64", n, variant=1 | 1 << 10)
