@@ -224,10 +224,13 @@ def _stream_scratch(nbytes, device, stream):
     enqueued.  None if nbytes is 0, the stream is not a torch stream of that device, or the
     device has no room for it."""
     torch = _torch()
-    stream = torch.cuda.current_stream() if stream is None else stream
-    if nbytes == 0 or getattr(stream, "device", None) != device:
+    if nbytes == 0:
         return None
     try:
+        if stream is None:  # the current stream of the current device
+            return empty_bytes(nbytes, device) if device.index == torch.cuda.current_device() else None
+        if getattr(stream, "device", None) != device:
+            return None
         with torch.cuda.stream(stream):
             return empty_bytes(nbytes, device)
     except torch.OutOfMemoryError:
