@@ -134,3 +134,36 @@ def test_npr_rejects_bad_arguments(asq):
     assert call([(0, 0, 0, 0)], gg=g[1:]) == asq.ASQ_EINVAL  # misaligned
     assert call([(0, 0, 0, 0)]) == asq.ASQ_OK
     torch.cuda.synchronize()
+
+
+def _partner(op):
+    return (op[0] ^ 1, op[1], op[2] ^ 1, op[3])
+
+
+def _op_lists():
+    rng = np.random.Generator(np.random.PCG64(27))
+    pool = [tuple(o) for o in rng.integers(0, 16, size=(60, 4)).tolist()]
+    alone = []
+    for o in pool:
+        if o not in alone and _partner(o) not in alone:
+            alone.append(o)
+    mixed = alone[:12] + [_partner(o) for o in alone[:12]] + alone[12:17]
+    rng.shuffle(mixed)
+    return {"one": alone[:1], "one pair": [alone[0], _partner(alone[0])],
+            "eight slots": [o for k in range(6) for o in (alone[k], _partner(alone[k]))] + alone[6:8],
+            "nine slots": [(s, 15, s, 15) for s in range(16)] + alone[3:4],
+            "no partners": alone[:16],  # a whole pass of the single form
+            "mixed, 29": [tuple(int(v) for v in o) for o in mixed],
+            "two launches": [tuple(int(v) for v in o) for o in mixed] + alone[17:25]}
+
+
+@pytest.mark.parametrize("label", list(_op_lists()))
+def test_npr_paired_operators(asq, label):
+    """Operators and their partners (gamma_x on both bilinears), with every combination of the
+    signs that relate them, against the oracle; the halved sums and differences of two operators
+    round by 1e-16 of the larger sum of products, as the operators one by one do."""
+    dims = (4, 4, 4, 4)
+    U = synth.thin_links(dims, 0.5, 28).reshape(256, 4, 3, 3)
+    G = random_props(dims, 29)
+    ops = _op_lists()[label]
+    compare(run_gpu(asq, dims, U, G, ops), oracle.npr_fourfermion(dims, U, G, ops), label)
