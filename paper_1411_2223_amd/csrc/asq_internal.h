@@ -149,7 +149,7 @@ constexpr int kPipeBit = 0x100;
 // non-temporal loads (the FP64-stored tiers always stream at one column).
 constexpr int kStreamBit = 0x200;
 constexpr int kOrderShift = 12;
-// Pipelined launches on the solvers' native layouts: each block first copies
+// Pipelined launches: each block first copies
 // the input records of its columns within three y-rows of its sites into LDS
 // (the window every x hop and every non-wrapping y hop reads), and those hops
 // read LDS instead of the caches.

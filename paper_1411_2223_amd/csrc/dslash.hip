@@ -15,8 +15,7 @@ bool variant_built(int link_kind, int in_kind, int rtile) {
   if ((rtile & ~(0xff | kPipeBit | kStreamBit | kLdsBit | (3 << kOrderShift) | kGlobalSweepBit | (3 << kChunkShift))) !=
       0)
     return false;
-  // the LDS window: pipelined loop, streamed links only at one column (native
-  // layouts only: the public operator on canonical vectors refuses it)
+  // the LDS window: pipelined loop, streamed links only at one column
   if ((rtile & kLdsBit) && (!(rtile & kPipeBit) || ((rtile & kStreamBit) && cols != 1))) return false;
   if ((rtile & (3 << kChunkShift)) && !(rtile & kGlobalSweepBit)) return false;  // runs only within a sweep
   // streamed links: one column, and not the FP64-stored tiers (which always stream there)

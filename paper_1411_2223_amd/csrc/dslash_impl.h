@@ -761,31 +761,27 @@ int pick_r(int rtile, const DslashArgs& a, hipStream_t s) {
   const int ord = rtile_order(rtile);
   const int gs = sweep_chunk_of(rtile);
   if (rtile & kLdsBit) {
-    // the LDS window: pipelined loop, native layouts; one column with ordinary
-    // or streamed links, or a tile of 2 to 12 columns
-    constexpr bool canon = std::is_same<InT, VecF64C>::value || std::is_same<InT, VecF32C>::value ||
-                           std::is_same<InT, VecF16C>::value;
+    // the LDS window: pipelined loop; one column with ordinary or streamed links, or a
+    // tile of 2 to 12 columns.  (On the canonical layouts only the tuner takes it:
+    // 96 FP16 columns at 20^3 x 64 0.775 -> 0.718 ms, 12 with 16-bit links at 48^3 x 96
+    // 1.97 -> 1.89, 12 FP64 columns at 16^3 x 32 68 -> 65 us.)
     constexpr bool f64_links = std::is_same<Link, LinkF64R18>::value || std::is_same<Link, LinkF64F32>::value;
-    if constexpr (canon) {
-      return ASQ_EINVAL;
-    } else {
-      if (!pipe) return ASQ_EINVAL;
-      if (rtile & kStreamBit) {
-        if constexpr (f64_links) return ASQ_EINVAL;
-        else return (rtile & 0xff) == 1 ? go<Streamed<Link>, InT, OutT, 1, EPI, true, true>(a, ord, gs, s) : ASQ_EINVAL;
-      }
-      switch (rtile & 0xff) {
-        case 1: return go<Link, InT, OutT, 1, EPI, true, true>(a, ord, gs, s);
-        case 2: return go<Link, InT, OutT, 2, EPI, true, true>(a, ord, gs, s);
-        case 4: return go<Link, InT, OutT, 4, EPI, true, true>(a, ord, gs, s);
-        case 6: return go<Link, InT, OutT, 6, EPI, true, true>(a, ord, gs, s);
-        case 8: return go<Link, InT, OutT, 8, EPI, true, true>(a, ord, gs, s);
-        case 12:
-          if constexpr (InT::kind == VEC_F64) return ASQ_EINVAL;
-          else return go<Link, InT, OutT, 12, EPI, true, true>(a, ord, gs, s);
-      }
-      return ASQ_EINVAL;
+    if (!pipe) return ASQ_EINVAL;
+    if (rtile & kStreamBit) {
+      if constexpr (f64_links) return ASQ_EINVAL;
+      else return (rtile & 0xff) == 1 ? go<Streamed<Link>, InT, OutT, 1, EPI, true, true>(a, ord, gs, s) : ASQ_EINVAL;
     }
+    switch (rtile & 0xff) {
+      case 1: return go<Link, InT, OutT, 1, EPI, true, true>(a, ord, gs, s);
+      case 2: return go<Link, InT, OutT, 2, EPI, true, true>(a, ord, gs, s);
+      case 4: return go<Link, InT, OutT, 4, EPI, true, true>(a, ord, gs, s);
+      case 6: return go<Link, InT, OutT, 6, EPI, true, true>(a, ord, gs, s);
+      case 8: return go<Link, InT, OutT, 8, EPI, true, true>(a, ord, gs, s);
+      case 12:
+        if constexpr (InT::kind == VEC_F64) return ASQ_EINVAL;
+        else return go<Link, InT, OutT, 12, EPI, true, true>(a, ord, gs, s);
+    }
+    return ASQ_EINVAL;
   }
   if (rtile & kStreamBit) {
     // links streamed past the caches: one column, FP32 and 16-bit tiers (the

@@ -720,6 +720,10 @@ extern "C" int asqtad_dslash_eo_variant(const asq_gauge* g, int out_parity, int 
     set_last_error("asqtad_dslash_eo_variant: unknown variant code");
     return ASQ_EINVAL;
   }
+  if (!native && !(v & kMfmaBit) && (v & kLdsBit)) {
+    set_last_error("asqtad_dslash_eo_variant: the LDS window takes the native layout only");
+    return ASQ_EINVAL;
+  }
   if (!native && (v & kMfmaBit)) {
     set_last_error("asqtad_dslash_eo_variant: the matrix-core form takes the native layout only");
     return ASQ_EINVAL;

@@ -168,9 +168,8 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
       for (size_t q = 0; q < n; ++q)
         if ((cands[q] & 0xff) == 1 && variant_built(link, in, cands[q] | kStreamBit)) cands.push_back(cands[q] | kStreamBit);
     }
-    // and every pipelined candidate with the LDS window (the canonical layouts
-    // refuse it, and so do windows too large for LDS; a candidate that fails to
-    // launch is skipped)
+    // and every pipelined candidate with the LDS window (windows too large for LDS are
+    // refused; a candidate that fails to launch is skipped)
     {
       const size_t n = cands.size();
       for (size_t q = 0; q < n; ++q)

@@ -383,3 +383,30 @@ def test_native_relayout_roundtrip(asq, prec):
     if prec == "f64":
         nat = n.cpu().numpy().reshape(nrhs, 3, half, 2)
         assert np.array_equal(nat[..., 0] + 1j * nat[..., 1], v.transpose(0, 2, 1))
+
+
+# a ragged last block whose window ends early; rows and planes that wrap; windows past both ends
+@pytest.mark.parametrize("dims", [(6, 4, 10, 6), (4, 8, 4, 18), (12, 6, 8, 10)])
+@pytest.mark.parametrize("precs,recon,tiers", [(("f64", "f32"), 18, ("f64", "f32", "f16")),
+                                               (("f32", "f16"), 12, ("f32", "f16")), (("f64",), 18, ("f32", "f16"))])
+def test_lds_window_on_canonical_vectors(asq, monkeypatch, dims, precs, recon, tiers):
+    """The public operator with the LDS window (the tuner's choice; forced here) gives the plain
+    kernel's bits on the canonical layouts, for every tile width, and is no code of the variant call."""
+    monkeypatch.setenv("ASQ_TUNE", "0")
+    fat, lng = synth.make_gauge(dims, 0.3, 91)
+    g = asq.Gauge(dims, fat, lng, precs=precs, recon=recon)
+    n = 13
+    b = asq.vec_to_device(synth.make_sources(dims, n, 92))
+    for prec in tiers:
+        v = b if prec == "f64" else asq.vec_convert(b, n * g.half, "f64", prec)
+        monkeypatch.delenv("ASQ_VARIANT", raising=False)
+        want = [g.dslash(p, v, prec, n).cpu().numpy().tobytes() for p in (0, 1)]
+        for cols in (1, 2, 4, 6, 8, 12):
+            for sweep, stream in ((False, False), (True, False), (False, cols == 1)):
+                print(f"canonical lds {dims} {precs} {prec} cols={cols} sweep={sweep} stream={stream}", flush=True)
+                code = asq.variant_code(cols, True, 1, lds=True, sweep=sweep, chunk=1 if sweep else 0, stream=stream)
+                monkeypatch.setenv("ASQ_VARIANT", str(code))
+                for p in (0, 1):
+                    assert g.dslash(p, v, prec, n).cpu().numpy().tobytes() == want[p]
+        with pytest.raises(asq.AsqError):
+            g.dslash(1, v, prec, n, variant=asq.variant_code(2, True, lds=True))
