@@ -156,6 +156,7 @@ def load():
             f = getattr(L, name)
             f.restype = res
             f.argtypes = args
+            globals()[name] = f  # the functions themselves from here on
         _lib = L
     return _lib
 
@@ -189,9 +190,13 @@ def _torch():
 
 
 def stream_ptr(stream=None):
+    if stream is not None:
+        return ctypes.c_void_p(stream.cuda_stream)
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # no Stream object: 0.3 instead of 2.5 us
+    if raw is not None:
+        return ctypes.c_void_p(raw(torch.cuda.current_device()))
+    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 VEC_SITE_BYTES = {"f64": 48, "f32": 24, "f16": 16}

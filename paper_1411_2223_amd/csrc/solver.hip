@@ -464,6 +464,16 @@ static void set_stall(ColState* host, int ncol, int mode) {
   }
 }
 
+// Whether a column is over, or will be within `iters` more iterations if |r| keeps
+// falling as it did over the last block (rr0: |r|^2 one block before S).
+static bool ends_within(const ColState& S, double rr0, int iters) {
+  if (!S.active) return true;
+  const double want = S.tol * S.tol * S.bb;
+  if (S.rr <= want) return true;
+  if (!(rr0 > S.rr) || !(want > 0)) return false;
+  return S.iters + iters >= S.maxiter || log(S.rr / want) <= log(rr0 / S.rr);
+}
+
 }  // namespace asq
 
 using namespace asq;
@@ -515,14 +525,14 @@ int asq::solve_batch(const asq_gauge* g, int nrhs, const double* masses, const d
 
   const int poll = params->poll_iters > 0 ? params->poll_iters : 8;
   hipGraphExec_t exec = nullptr;
-  if (params->use_graph) {
-    rc = capture_block(B, poll, H.cap, &exec);
-    if (rc) return rc;
-  }
   int slot = 0, pending = -1, last = -1;
   long blocks = 0;
   const long max_blocks = (long)params->maxiter / poll + 4;
+  std::vector<double> seen(nrhs, 0.0);  // |r|^2 of each column at the previous poll
   for (;;) {
+    // the first block is enqueued launch by launch, and the graph captured while the
+    // GPU works on it
+    if (params->use_graph && blocks == 1 && (rc = capture_block(B, poll, H.cap, &exec))) return rc;
     if (exec) {
       hipError_t e = hipGraphLaunch(exec, s);
       if (e != hipSuccess) {
@@ -539,9 +549,22 @@ int asq::solve_batch(const asq_gauge* g, int nrhs, const double* masses, const d
     last = slot;
     if (pending >= 0) {
       ASQ_HIP_TRY(hipEventSynchronize(H.ev[pending]));
-      bool any = false;
-      for (int c = 0; c < nrhs; ++c) any |= mirror[pending][c].active != 0;
+      bool any = false, ends = true;
+      for (int c = 0; c < nrhs; ++c) {
+        const ColState& S = mirror[pending][c];
+        any |= S.active != 0;
+        ends = ends && ends_within(S, seen[c], poll);
+        seen[c] = S.rr;
+      }
       if (!any) break;
+      if (ends) {
+        // the block in flight is likely the last: look at it before enqueueing another
+        // (a block of masked launches costs 100 to 150 us)
+        ASQ_HIP_TRY(hipEventSynchronize(H.ev[last]));
+        any = false;
+        for (int c = 0; c < nrhs; ++c) any |= mirror[last][c].active != 0;
+        if (!any) break;
+      }
     }
     if (blocks > max_blocks + 2) break;  // the device enforces maxiter; this only bounds the loop
     pending = slot;

@@ -10,6 +10,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <array>
 #include <map>
 #include <mutex>
 #include <string>
@@ -24,11 +25,34 @@ std::mutex g_mu;
 std::map<std::string, int> g_cache;
 bool g_loaded = false;
 
+// The architecture name of a device, asked for once: the query costs more than the
+// rest of a lookup.
+std::string arch_of(int device) {
+  static std::mutex mu;
+  static std::map<int, std::string> names;
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = names.find(device);
+  if (it != names.end()) return it->second;
+  hipDeviceProp_t prop;
+  if (hipGetDeviceProperties(&prop, device) != hipSuccess) return "gfx";
+  return names[device] = prop.gcnArchName;
+}
+
+// What a configuration's string key is made of.  g_quick maps it to the recorded
+// variant, so that a call that was tuned before builds no string (a public operator
+// call at 8^4 takes 5.3 us on the GPU; the two string lookups took 1.6 us of its host
+// time).  Filled from g_cache and emptied when that changes, under g_mu.
+using QuickKey = std::array<int, 10>;
+std::map<QuickKey, int> g_quick;
+
+QuickKey quick_key(const asq_gauge* g, int link, int in, int out, int epi, int ncol) {
+  return {g->device, g->geom.X, g->geom.Y, g->geom.Z, g->geom.T, link, in, out, epi, ncol};
+}
+
 std::string key_of(const asq_gauge* g, int link, int in, int out, int epi, int ncol) {
   char buf[160];
-  hipDeviceProp_t prop;
-  const char* arch = "gfx";
-  if (hipGetDeviceProperties(&prop, g->device) == hipSuccess) arch = prop.gcnArchName;
+  const std::string name = arch_of(g->device);
+  const char* arch = name.c_str();
   snprintf(buf, sizeof(buf), "%s/%dx%dx%dx%d/L%d/I%d/O%d/E%d/N%d", arch, g->geom.X, g->geom.Y, g->geom.Z,
            g->geom.T, link, in, out, epi, ncol);
   for (char* c = buf; *c; ++c)
@@ -64,6 +88,17 @@ void save_cache_locked() {
   fclose(f);
 }
 
+// The recorded variant of a configuration, or -1.
+int recorded_locked(const asq_gauge* g, int link, int in, int out, int epi, int ncol) {
+  load_cache_locked();
+  const QuickKey q = quick_key(g, link, in, out, epi, ncol);
+  auto f = g_quick.find(q);
+  if (f != g_quick.end()) return f->second;
+  auto it = g_cache.find(key_of(g, link, in, out, epi, ncol));
+  if (it == g_cache.end() || it->second < 0) return -1;
+  return g_quick[q] = it->second;
+}
+
 int default_rtile(int link, int ncol) {
   if (ncol <= 1) return 1;
   if (link == LINK_F64_R18) return 2;
@@ -95,13 +130,12 @@ int tuned_rtile(const asq_gauge* g, int link, int in, int out, int epi, int ncol
   if (fv >= 0 && !(fv & kMfmaBit) && (fv & 0xff) <= (ncol > 1 ? ncol : 1) && variant_fits(g->geom, in, fv)) return fv;
   if (fv >= 0 && (fv & kMfmaBit) && ncol > kFoldAlphaMaxTile) return fv;
   std::lock_guard<std::mutex> lk(g_mu);
-  load_cache_locked();
-  auto it = g_cache.find(key_of(g, link, in, out, epi, ncol));
+  const int v = recorded_locked(g, link, in, out, epi, ncol);
   // a cache file may come from another build: only variants the tuner itself
   // could have chosen are taken from it
-  if (it != g_cache.end() && variant_built(link, in, it->second) && !(it->second & kMfmaBit) &&
-      (it->second & 0xff) <= (ncol > 1 ? ncol : 1) && variant_fits(g->geom, in, it->second))
-    return it->second;
+  if (v >= 0 && variant_built(link, in, v) && !(v & kMfmaBit) && (v & 0xff) <= (ncol > 1 ? ncol : 1) &&
+      variant_fits(g->geom, in, v))
+    return v;
   return default_rtile(link, ncol);
 }
 
@@ -122,12 +156,12 @@ bool tune_pending(const asq_gauge* g, int link, int in, int ncol, int epi_timed)
 // (timings taken while other work may share the device).
 int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_buf, void* out_buf,
                 hipStream_t s, int epi_timed, bool persist) {
-  const std::string kp = key_of(g, link, in, in, epi_timed, ncol);
   {
     std::lock_guard<std::mutex> lk(g_mu);
-    load_cache_locked();
-    if (g_cache.count(kp)) return ASQ_OK;
+    if (recorded_locked(g, link, in, in, epi_timed, ncol) >= 0) return ASQ_OK;
+    if (g_cache.count(key_of(g, link, in, in, epi_timed, ncol))) return ASQ_OK;
   }
+  const std::string kp = key_of(g, link, in, in, epi_timed, ncol);
   int best = default_rtile(link, ncol);
   int best_update = best;  // the UPDATE epilogue's pick: no tile wider than 8 columns
   if (tuning_on()) {
@@ -221,6 +255,7 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
     (void)hipEventDestroy(e1);
   }
   std::lock_guard<std::mutex> lk(g_mu);
+  g_quick.clear();
   if (epi_timed == EPI_CANON) {
     g_cache[kp] = best;
   } else {
