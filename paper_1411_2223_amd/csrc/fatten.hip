@@ -366,9 +366,10 @@ __device__ __forceinline__ void stage_coords(const StageArgs& A, int i, Pos& p) 
 // (mu, site, part) of this thread.  A block is four waves: the four directions
 // over the same 64 sites, or 256 sites of one direction; `parts` blocks next to
 // each other in dispatch order share its sites.
-__device__ __forceinline__ bool stage_site(const StageArgs& A, int parts, int& mu, int& m, int& part, Pos& p) {
+__device__ __forceinline__ bool stage_site(const StageArgs& A, int parts, int blocks, int& mu, int& m, int& part,
+                                           Pos& p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lin = xcd_remap((int)blockIdx.x, (int)gridDim.x);
+  const int lin = xcd_remap((int)blockIdx.x, blocks);
   const int blk = lin / parts;
   part = lin % parts;
   m = A.nmu == 4 ? wave : 0;
@@ -471,10 +472,32 @@ __device__ __forceinline__ void scale_add(M3& C, double s, double t, const M3& U
 // the q-th axis off mu
 __device__ __forceinline__ int axis_off(int mu, int q) { return q + (q >= mu ? 1 : 0); }
 
-__global__ void __launch_bounds__(256) fat_core_kernel(const StageArgs A) {
+// L_mu(x) = cN U_mu(x) U_mu(x+mu) U_mu(x+2mu) for the 64 sites of block blk, a wave per mu.
+__device__ __forceinline__ void long_links(const StageArgs& A, int blk) {
+  __shared__ double2 tile[kFatSites][37];
+  const int lane = threadIdx.x & 63;
+  const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  Pos p;
+  stage_coords(A, min(blk * kFatSites + lane, A.n - 1), p);
+  const Slots U = link_slot(A, mu);
+  M3 L = zero_m3();
+  const M3 P = mul_nn(slot_load(U, p.i), slot_load(U, p.i + hop(A, p, mu, 1)));
+  acc_nn(L, A.cN, P, slot_load(U, p.i + hop(A, p, mu, 2)));
+#pragma unroll
+  for (int k = 0; k < 9; ++k) tile[lane][mu * 9 + k] = make_double2(L.e[k / 3][k % 3].re, L.e[k / 3][k % 3].im);
+  __syncthreads();
+  const int s0 = blk * kFatSites;
+  const int nrun = min(kFatSites, A.n - s0) * 36;
+  for (int e = threadIdx.x; e < nrun; e += 256) A.lng[(size_t)s0 * 36 + e] = tile[e / 36][e % 36];
+}
+
+// Stage 1; blocks past the stage's own `ncore` form the long links (they need the thin
+// links only, and a launch of their own would cost small lattices 4 us).
+__global__ void __launch_bounds__(256) fat_core_kernel(const StageArgs A, int ncore) {
+  if ((int)blockIdx.x >= ncore) return long_links(A, xcd_remap((int)blockIdx.x - ncore, (int)gridDim.x - ncore));
   int mu, m, q;
   Pos p;
-  const bool valid = stage_site(A, 3, mu, m, q, p);
+  const bool valid = stage_site(A, 3, ncore, mu, m, q, p);
   const Slots U = link_slot(A, mu);
   M3 C = zero_m3();
 #pragma unroll 1
@@ -486,7 +509,7 @@ __global__ void __launch_bounds__(256) fat_core_kernel(const StageArgs A) {
 __global__ void __launch_bounds__(256) fat_five_kernel(const StageArgs A) {
   int mu, m, q;  // q: nu
   Pos p;
-  const bool valid = stage_site(A, 3, mu, m, q, p);
+  const bool valid = stage_site(A, 3, (int)gridDim.x, mu, m, q, p);
   M3 C = zero_m3();
 #pragma unroll 1
   for (int r = 0; r < 4; ++r) {  // rho = q + 1, q + 2 (mod 3), both signs; c the axis left
@@ -535,25 +558,6 @@ __global__ void __launch_bounds__(192) fat_link_kernel(const StageArgs A) {
     A.fat[((size_t)(s0 + j) * 4 + mu) * 9 + k] =
         make_double2(fmaR(A.c1, u.x, a.x + b.x + c.x), fmaR(A.c1, u.y, a.y + b.y + c.y));
   }
-}
-
-// L_mu(x) = cN U_mu(x) U_mu(x+mu) U_mu(x+2mu) from the site-fastest copy, a wave per mu.
-__global__ void __launch_bounds__(256) long_soa_kernel(const StageArgs A) {
-  int mu, m, part;
-  Pos p;
-  stage_site(A, 1, mu, m, part, p);
-  const Slots U = link_slot(A, mu);
-  M3 L = zero_m3();
-  const M3 P = mul_nn(slot_load(U, p.i), slot_load(U, p.i + hop(A, p, mu, 1)));
-  acc_nn(L, A.cN, P, slot_load(U, p.i + hop(A, p, mu, 2)));
-  __shared__ double2 tile[kFatSites][37];
-#pragma unroll
-  for (int k = 0; k < 9; ++k)
-    tile[threadIdx.x & 63][mu * 9 + k] = make_double2(L.e[k / 3][k % 3].re, L.e[k / 3][k % 3].im);
-  __syncthreads();
-  const int s0 = xcd_remap((int)blockIdx.x, (int)gridDim.x) * kFatSites;
-  const int nrun = min(kFatSites, A.n - s0) * 36;
-  for (int e = threadIdx.x; e < nrun; e += 256) A.lng[(size_t)s0 * 36 + e] = tile[e / 36][e % 36];
 }
 
 // Canonical thin links -> the site-fastest copy.  A block moves 64 sites: it
@@ -889,17 +893,13 @@ extern "C" int asqtad_build_links_work(const int dims[4], const double* thin_dev
   thin_soa_kernel<<<nb64, 256, 0, s>>>(f.thin, soa, f.V, true);
   ASQ_HIP_TRY(hipGetLastError());
   for (a.mu0 = 0; a.mu0 < 4; a.mu0 += a.nmu) {
-    fat_core_kernel<<<3 * nb, 256, 0, s>>>(a);
+    fat_core_kernel<<<3 * nb + (a.mu0 == 0 ? nb64 : 0), 256, 0, s>>>(a, (int)(3 * nb));
     ASQ_HIP_TRY(hipGetLastError());
     fat_five_kernel<<<3 * nb, 256, 0, s>>>(a);
     ASQ_HIP_TRY(hipGetLastError());
     fat_link_kernel<<<a.nmu * nb64, 192, 0, s>>>(a);
     ASQ_HIP_TRY(hipGetLastError());
   }
-  a.mu0 = 0;
-  a.nmu = 4;
-  long_soa_kernel<<<nb64, 256, 0, s>>>(a);
-  ASQ_HIP_TRY(hipGetLastError());
   return ASQ_OK;
 }
 
