@@ -43,36 +43,48 @@ struct alignas(64) ShiftState {
   int status;
 };
 
-// After the base's beta reduction: the shifted scalars of every shift column.
-__global__ void shift_scalars_kernel(ShiftState* sh, const ColState* st, int nsh) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= nsh) return;
-  ShiftState T = sh[j];
-  const ColState& S = st[T.src];
-  T.upd = 0;
-  if (T.active && S.iters != T.base_iters) {
-    T.base_iters = S.iters;
-    const double ak = S.alpha, bk = T.b_prev, bk1 = S.beta;
-    const double z = T.zeta, zp = T.zeta_prev;
-    const double den = ak * bk * (zp - z) + zp * T.a_prev * (1.0 + T.ds * ak);
-    const double zn = z * zp * T.a_prev / den;
-    const double q = zn / z;
-    if (!isfinite(zn) || !isfinite(q)) {
-      T.active = 0;
-      T.status = ASQ_ENAN;
-    } else {
-      T.alpha = ak * q;
-      T.beta = bk1 * q * q;
-      T.zeta_prev = z;
-      T.zeta = zn;
-      T.a_prev = ak;
-      T.b_prev = bk1;
-      T.upd = 1;
-      T.iters += 1;
-      if (fabs(zn) * sqrt(S.rr) <= T.tol * sqrt(S.bb) || !S.active) T.active = 0;
-    }
+// The base column's beta step and the shifted scalars of its shift columns, a block
+// per base column (as one launch each they took 4.6 and 4.1 us of a 16^3 x 32
+// iteration of 6 sources).  SUB: partials per site block in pr (|r|^2).
+template <int SUB>
+__global__ void __launch_bounds__(kBlock) beta_shift_kernel(ColState* st, const double* pr, int nblk, ShiftState* sh,
+                                                            int nsh) {
+  const int c = blockIdx.x;
+  ColState& S = st[c];
+  if (S.active != 0 && S.frozen == 0) {  // uniform over the block
+    __shared__ double part[kBlock / 64];
+    const double s = block_sum(strided_sum<SUB>(pr + (size_t)c * nblk * SUB, nblk), part);
+    if (threadIdx.x == 0) finalize_column(S, s, OP_BETA);
   }
-  sh[j] = T;
+  __syncthreads();
+  for (int j = (int)threadIdx.x; j < nsh; j += kBlock) {
+    ShiftState T = sh[j];
+    if (T.src != c) continue;
+    T.upd = 0;
+    if (T.active && S.iters != T.base_iters) {
+      T.base_iters = S.iters;
+      const double ak = S.alpha, bk = T.b_prev, bk1 = S.beta;
+      const double z = T.zeta, zp = T.zeta_prev;
+      const double den = ak * bk * (zp - z) + zp * T.a_prev * (1.0 + T.ds * ak);
+      const double zn = z * zp * T.a_prev / den;
+      const double q = zn / z;
+      if (!isfinite(zn) || !isfinite(q)) {
+        T.active = 0;
+        T.status = ASQ_ENAN;
+      } else {
+        T.alpha = ak * q;
+        T.beta = bk1 * q * q;
+        T.zeta_prev = z;
+        T.zeta = zn;
+        T.a_prev = ak;
+        T.b_prev = bk1;
+        T.upd = 1;
+        T.iters += 1;
+        if (fabs(zn) * sqrt(S.rr) <= T.tol * sqrt(S.bb) || !S.active) T.active = 0;
+      }
+    }
+    sh[j] = T;
+  }
 }
 
 // x_j += alpha_j p_j; p_j = zeta r_base + beta_j p_j (x_j, p_j FP32; r in the RT tier).
@@ -130,10 +142,13 @@ size_t shift_bytes(const asq_gauge* g, int nsh) {
 int enqueue_ms_block(const Batch& B, ShiftState* sh, int nsh, float* xs, float* ps, int iters, hipStream_t s) {
   const int half = B.g->geom.half;
   for (int k = 0; k < iters; ++k) {
-    int rc = enqueue_iteration(B, s);
+    int rc = enqueue_iteration(B, s, B.st, B.st, nsh > 0);
     if (rc) return rc;
     if (nsh > 0) {
-      shift_scalars_kernel<<<(unsigned)((nsh + 63) / 64), 64, 0, s>>>(sh, B.st, nsh);
+      if (partial_sub(B.rt_sloppy_update) == 1)
+        beta_shift_kernel<1><<<(unsigned)B.ncol, kBlock, 0, s>>>(B.st, B.partials, B.g->nblk, sh, nsh);
+      else
+        beta_shift_kernel<kWaves><<<(unsigned)B.ncol, kBlock, 0, s>>>(B.st, B.partials, B.g->nblk, sh, nsh);
       const dim3 grid((unsigned)B.g->nblk, (unsigned)nsh);
       if (B.rt == VEC_F64) shift_update_kernel<VecF64><<<grid, kBlock, 0, s>>>(sh, xs, ps, B.r, half);
       else shift_update_kernel<VecF32><<<grid, kBlock, 0, s>>>(sh, xs, ps, B.r, half);

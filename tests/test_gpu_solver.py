@@ -593,3 +593,21 @@ def test_split_form_is_bitwise_the_plain_form(asq, monkeypatch, dims, n, precs, 
                         k: t[k] for k in ("iters", "reliable_updates", "converged", "true_resid")}
     with pytest.raises(asq.AsqError):  # the tuner's own choice: not a code of the variant call
         g.dslash(1, b, "f64", n, variant=1 | 1 << 10)
+
+
+@pytest.mark.parametrize("dims,nsrc,masses", [((4, 4, 4, 4), 1, (0.1, 0.2)), ((6, 4, 10, 6), 3, (0.3, 0.1, 0.2)),
+                                              ((4, 6, 8, 16), 2, (0.15,))])
+def test_multishift_with_split_form_is_bitwise_the_plain_form(asq, monkeypatch, dims, nsrc, masses):
+    """The shifted solver's beta step reads either kind of |r|^2 partials: a partial per site block,
+    or per wave of the split form.  The smallest mass first, last and alone (no shifts)."""
+    monkeypatch.setenv("ASQ_TUNE", "0")
+    fat, lng = synth.make_gauge(dims, 0.3, 79)
+    g = asq.Gauge(dims, fat, lng, precs=("f64", "f32"), recon=18)
+    b = asq.vec_to_device(synth.make_sources(dims, nsrc, 80))
+    print(f"multishift split {dims} nsrc={nsrc} masses={masses}", flush=True)
+    want = g.solve_multishift(masses, b)
+    monkeypatch.setenv("ASQ_VARIANT", str(1 | 1 << 10))
+    got = g.solve_multishift(masses, b)
+    assert want.rc == 0 and got.rc == 0
+    assert got.x.cpu().numpy().tobytes() == want.x.cpu().numpy().tobytes()
+    assert [s["iters"] for s in got.stats] == [s["iters"] for s in want.stats]
