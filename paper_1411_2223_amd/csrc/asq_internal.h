@@ -184,6 +184,15 @@ constexpr int kMfmaTile = 32;
 // 13.1 us plain); chosen by the tuner only, the public variant call does not take it.
 constexpr int kSplitCode = 1 | (1 << kChunkShift);
 constexpr long kSplitMaxBlocks = 512;
+// A tile of three columns (pipelined loop, FP32 and FP16 vectors): coded as the streamed
+// form of six columns, which no other variant uses.  Sources come in threes (a column per
+// colour), where a tile of four leaves a lane idle and two tiles read the links twice:
+// FP32 at 16^3 x 32, 3 columns 18.1 -> 16.5 us, 6 columns 23.9 -> 22.7; chosen by the
+// tuner only, the public variant call does not take it.
+constexpr int kThreeCols = 6 | kStreamBit;
+inline bool three_cols(int rtile) { return !(rtile & kMfmaBit) && (rtile & (0xff | kStreamBit)) == kThreeCols; }
+// Columns per thread of a variant code.
+inline int tile_cols(int rtile) { return three_cols(rtile) ? 3 : rtile & 0xff; }
 inline int partial_sub(int rtile) { return rtile == kSplitCode ? kWaves : 1; }
 inline int rtile_order(int rtile) { return (rtile >> kOrderShift) & 3; }
 inline int order_group(int order, int nblk) { return order == 0 ? 0 : (order == 1 ? 16 : (order == 2 ? 64 : nblk)); }
@@ -198,9 +207,14 @@ inline int make_rtile(int cols, bool pipe, int order, bool global_sweep = false,
          (global_sweep ? kGlobalSweepBit | (chunk_code << kChunkShift) : 0);
 }
 // Widest column tile whose UPDATE launch may form alpha itself (DslashArgs::apa): its
-// partials are loaded before the hop loop.  (4-column tiles, which have no registers
-// for that and loaded them after it, made a 16^3 x 32 multi-shift solve 2 % slower.)
-constexpr int kFoldAlphaMaxTile = 2;
+// partials are loaded before the hop loop.  (3 columns: 6 and 9 columns at 16^3 x 32 18.1 ->
+// 17.9 and 22.4 -> 21.8 ms a solve, 3 at 16^3 x 64 37.5 -> 36.5.  4-column tiles, which have
+// no registers for that and loaded them after it, made a 16^3 x 32 multi-shift solve 2 % slower.)
+constexpr int kFoldAlphaMaxTile = 3;
+// Fewest blocks for which the tuner gives the UPDATE launch a tile of three columns: two per
+// CU.  With less its epilogue has too few waves to hide behind (3 columns at 16^3 x 32, 256
+// blocks: 13.0 ms a solve with two-column tiles, 13.2 with three; at 16^3 x 64 37.7 and 36.5).
+constexpr long kThreeUpdateMinBlocks = 512;
 
 // Tuned launch variant for a Dslash configuration.
 int tuned_rtile(const asq_gauge* g, int link_kind, int in_kind, int out_kind, int epi, int ncol);

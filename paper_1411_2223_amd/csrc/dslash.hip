@@ -5,7 +5,7 @@
 namespace asq {
 
 bool variant_built(int link_kind, int in_kind, int rtile) {
-  const int cols = rtile & 0xff;
+  const int cols = tile_cols(rtile);
   if (rtile & kMfmaBit) {
     // matrix-core form: one tile width, no pipelined form
     if ((rtile & ~(kMfmaBit | 0xff | (3 << kOrderShift))) != 0) return false;
@@ -15,9 +15,11 @@ bool variant_built(int link_kind, int in_kind, int rtile) {
   if ((rtile & ~(0xff | kPipeBit | kStreamBit | kLdsBit | (3 << kOrderShift) | kGlobalSweepBit | (3 << kChunkShift))) !=
       0)
     return false;
+  if (cols == 3 && (!three_cols(rtile) || !(rtile & kPipeBit) || in_kind == VEC_F64)) return false;
   // the LDS window: pipelined loop, streamed links only at one column
-  if ((rtile & kLdsBit) && (!(rtile & kPipeBit) || ((rtile & kStreamBit) && cols != 1))) return false;
+  if ((rtile & kLdsBit) && (!(rtile & kPipeBit) || ((rtile & kStreamBit) && cols != 1 && cols != 3))) return false;
   if ((rtile & (3 << kChunkShift)) && !(rtile & kGlobalSweepBit)) return false;  // runs only within a sweep
+  if (cols == 3) return true;
   // streamed links: one column, and not the FP64-stored tiers (which always stream there)
   if ((rtile & kStreamBit) && (cols != 1 || link_kind == LINK_F64_R18 || link_kind == LINK_F64_F32)) return false;
   return cols == 1 || cols == 2 || cols == 4 || cols == 6 || cols == 8 || (cols == 12 && in_kind != VEC_F64);
@@ -25,7 +27,7 @@ bool variant_built(int link_kind, int in_kind, int rtile) {
 
 bool variant_fits(const Geom& g, int in_kind, int rtile) {
   if (!(rtile & kLdsBit)) return true;
-  return (size_t)(rtile & 0xff) * lds_window(g.Xh) * vec_site_bytes(in_kind) <= kLdsWindowMax;
+  return (size_t)tile_cols(rtile) * lds_window(g.Xh) * vec_site_bytes(in_kind) <= kLdsWindowMax;
 }
 
 int launch_dslash(int link_kind, int in_kind, int out_kind, int epi, int rtile, const DslashArgs& a,

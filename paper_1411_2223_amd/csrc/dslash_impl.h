@@ -760,6 +760,12 @@ int pick_r(int rtile, const DslashArgs& a, hipStream_t s) {
   const bool pipe = (rtile & kPipeBit) != 0;
   const int ord = rtile_order(rtile);
   const int gs = sweep_chunk_of(rtile);
+  if (three_cols(rtile)) {
+    if constexpr (InT::kind == VEC_F64) return ASQ_EINVAL;
+    else if (!pipe) return ASQ_EINVAL;
+    else if (rtile & kLdsBit) return go<Link, InT, OutT, 3, EPI, true, true>(a, ord, gs, s);
+    else return go<Link, InT, OutT, 3, EPI, true>(a, ord, gs, s);
+  }
   if (rtile & kLdsBit) {
     // the LDS window: pipelined loop; one column with ordinary or streamed links, or a
     // tile of 2 to 12 columns.  (On the canonical layouts only the tuner takes it:

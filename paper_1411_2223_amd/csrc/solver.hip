@@ -144,7 +144,7 @@ void batch_pick_tiles(Batch& B) {
   B.rt64_plain = tuned_rtile(g, LINK_F64_R18, VEC_F64, VEC_F64, EPI_PLAIN, B.ncol);
   B.rt64_resid = tuned_rtile(g, LINK_F64_R18, VEC_F64, B.rt, EPI_RESID, B.ncol);
   const bool few = g->nblk <= kFoldMaxBlocks;
-  B.fold_alpha = few && !(B.rt_sloppy_update & kMfmaBit) && (B.rt_sloppy_update & 0xff) <= kFoldAlphaMaxTile &&
+  B.fold_alpha = few && !(B.rt_sloppy_update & kMfmaBit) && tile_cols(B.rt_sloppy_update) <= kFoldAlphaMaxTile &&
                  env_flag("ASQ_FOLD_ALPHA", true);
   B.fold_beta = few && (long)g->nblk * B.ncol <= kFoldMaxLaunch && env_flag("ASQ_FOLD_BETA", true);
 }
@@ -739,7 +739,7 @@ extern "C" int asqtad_dslash_eo_variant(const asq_gauge* g, int out_parity, int 
   const bool native = (variant & ASQ_VARIANT_NATIVE) != 0;
   int v = variant & ~ASQ_VARIANT_NATIVE;
   if (native && v == 0) v = -1;  // the tuned variant on native vectors
-  if (v == kSplitCode) {
+  if (v == kSplitCode || (v >= 0 && three_cols(v))) {
     set_last_error("asqtad_dslash_eo_variant: unknown variant code");
     return ASQ_EINVAL;
   }

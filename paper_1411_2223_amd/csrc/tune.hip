@@ -127,13 +127,13 @@ int tuned_rtile(const asq_gauge* g, int link, int in, int out, int epi, int ncol
   // a forced tile wider than the batch, or whose LDS window does not fit this
   // lattice, is ignored, except the matrix-core form, which masks its idle
   // columns; that form is for many columns and not forced on one or two
-  if (fv >= 0 && !(fv & kMfmaBit) && (fv & 0xff) <= (ncol > 1 ? ncol : 1) && variant_fits(g->geom, in, fv)) return fv;
-  if (fv >= 0 && (fv & kMfmaBit) && ncol > kFoldAlphaMaxTile) return fv;
+  if (fv >= 0 && !(fv & kMfmaBit) && tile_cols(fv) <= (ncol > 1 ? ncol : 1) && variant_fits(g->geom, in, fv)) return fv;
+  if (fv >= 0 && (fv & kMfmaBit) && ncol > 2) return fv;
   std::lock_guard<std::mutex> lk(g_mu);
   const int v = recorded_locked(g, link, in, out, epi, ncol);
   // a cache file may come from another build: only variants the tuner itself
   // could have chosen are taken from it
-  if (v >= 0 && variant_built(link, in, v) && !(v & kMfmaBit) && (v & 0xff) <= (ncol > 1 ? ncol : 1) &&
+  if (v >= 0 && variant_built(link, in, v) && !(v & kMfmaBit) && tile_cols(v) <= (ncol > 1 ? ncol : 1) &&
       variant_fits(g->geom, in, v))
     return v;
   return default_rtile(link, ncol);
@@ -188,14 +188,14 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
     for (int gs = 0; gs < 2; ++gs)
       for (int order = 0; order < 4; ++order)
         for (int pipe = 0; pipe < 2; ++pipe)
-          for (int cols : {1, 2, 4, 6, 8, 12})
-            if (order == 0 || (ncol + cols - 1) / cols >= 2) cands.push_back(make_rtile(cols, pipe, order, gs != 0));
+          for (int cols : {1, 2, kThreeCols, 4, 6, 8, 12})
+            if (order == 0 || ncol > tile_cols(cols)) cands.push_back(make_rtile(cols, pipe, order, gs != 0));
     // runs of 16, 64 or 256 blocks per XCD inside the sweep: pipelined loop, the
     // first two block orders
     for (int chunk = 1; chunk <= 3; ++chunk)
       for (int order = 0; order < 2; ++order)
-        for (int cols : {1, 2, 4, 6, 8, 12})
-          if (order == 0 || (ncol + cols - 1) / cols >= 2) cands.push_back(make_rtile(cols, true, order, true, chunk));
+        for (int cols : {1, 2, kThreeCols, 4, 6, 8, 12})
+          if (order == 0 || ncol > tile_cols(cols)) cands.push_back(make_rtile(cols, true, order, true, chunk));
     // one-column tiles with streamed links, where the tier has that form
     {
       const size_t n = cands.size();
@@ -224,7 +224,7 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
       return ok;
     };
     for (int r : cands) {
-      const int cols = r & 0xff;
+      const int cols = tile_cols(r);
       if (cols > 1 && cols > ncol) continue;  // a wider tile than the batch only wastes lanes
       if (!pair(r)) continue;  // warm-up
       // a candidate whose timing fails is skipped
@@ -246,7 +246,8 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
       // the UPDATE epilogue also keeps r, x and the direction of every column of
       // the tile live: the 12-column tile loses occupancy there that the plain
       // loop timed here does not show
-      if (cols <= 8 && ms < best_update_ms) {
+      const bool three_ok = cols != 3 || (long)g->nblk * ((ncol + 2) / 3) >= kThreeUpdateMinBlocks;
+      if (cols <= 8 && three_ok && ms < best_update_ms) {
         best_update_ms = ms;
         best_update = r;
       }

@@ -410,3 +410,47 @@ def test_lds_window_on_canonical_vectors(asq, monkeypatch, dims, precs, recon, t
                     assert g.dslash(p, v, prec, n).cpu().numpy().tobytes() == want[p]
         with pytest.raises(asq.AsqError):
             g.dslash(1, v, prec, n, variant=asq.variant_code(2, True, lds=True))
+
+
+# a ragged last block; tiles that the columns fill, leave one or two lanes of, or a single narrow tile
+@pytest.mark.parametrize("dims,n", [((6, 4, 10, 6), 3), ((4, 8, 4, 18), 7), ((12, 6, 8, 10), 8), ((4, 4, 4, 4), 6)])
+@pytest.mark.parametrize("precs,recon,tiers", [(("f64", "f32"), 18, ("f64", "f32", "f16")),
+                                               (("f32", "f16"), 12, ("f32", "f16")), (("f64",), 18, ("f32", "f16"))])
+def test_three_column_tile(asq, monkeypatch, dims, n, precs, recon, tiers):
+    """Tiles of three columns (the tuner's choice; forced here) give the plain kernel's bits, with and
+    without the LDS window and in every block order, and are no code of the variant call."""
+    monkeypatch.setenv("ASQ_TUNE", "0")
+    fat, lng = synth.make_gauge(dims, 0.3, 93)
+    g = asq.Gauge(dims, fat, lng, precs=precs, recon=recon)
+    b = asq.vec_to_device(synth.make_sources(dims, n, 94))
+    for prec in tiers:
+        v = b if prec == "f64" else asq.vec_convert(b, n * g.half, "f64", prec)
+        monkeypatch.delenv("ASQ_VARIANT", raising=False)
+        want = [g.dslash(p, v, prec, n).cpu().numpy().tobytes() for p in (0, 1)]
+        for lds in (False, True):
+            for order, sweep in ((0, False), (1, False), (2, True), (3, False)):
+                code = asq.variant_code(6, True, order, lds=lds, sweep=sweep, chunk=1 if sweep else 0) | 1 << 9
+                print(f"three columns {dims} n={n} {precs} {prec} lds={lds} order={order}", flush=True)
+                monkeypatch.setenv("ASQ_VARIANT", str(code))
+                for p in (0, 1):
+                    assert g.dslash(p, v, prec, n).cpu().numpy().tobytes() == want[p]
+        with pytest.raises(asq.AsqError):
+            g.dslash(1, v, prec, n, variant=code)
+
+
+@pytest.mark.parametrize("mode", ["mixed32", "mixed16"])
+def test_three_column_tile_in_the_solver(asq, monkeypatch, mode):
+    """The solver's fused forms of the three-column tile: the same x and iterations, bit for bit."""
+    monkeypatch.setenv("ASQ_TUNE", "0")
+    dims, masses = (6, 4, 10, 6), [0.1, 0.1, 0.2, 0.3, 0.1]
+    fat, lng = synth.make_gauge(dims, 0.3, 95)
+    g = asq.Gauge(dims, fat, lng, precs=("f64", "f32"), recon=18)
+    b = asq.vec_to_device(synth.make_sources(dims, len(masses), 96))
+    want = g.solve(masses, b, mode=mode)
+    assert want.rc == 0
+    for lds in (False, True):
+        print(f"three columns solve {mode} lds={lds}", flush=True)
+        monkeypatch.setenv("ASQ_VARIANT", str(asq.variant_code(6, True, 1, lds=lds) | 1 << 9))
+        got = g.solve(masses, b, mode=mode)
+        assert got.rc == 0 and got.x.cpu().numpy().tobytes() == want.x.cpu().numpy().tobytes()
+        assert [s["iters"] for s in got.stats] == [s["iters"] for s in want.stats]
