@@ -40,9 +40,9 @@ PEAK_FP32_PACKED_TFLOPS = 157.3
 PEAK_FP32_TFLOPS = 78.6
 # FP64 vector peak: 256 CU x 2.4 GHz x 128 FP64 flop/clk
 PEAK_FP64_TFLOPS = 78.6
-# SU(3) products per (site, direction) of the nested-staple link construction:
-# 6 x (4 x (2 x 2 + 2) + 2 + 2) for the fat link, 2 for the long link; 198 flops each
-LINK_BUILD_PRODUCTS = 170
+# SU(3) products per (site, direction) of the link construction in three stages of shared
+# staples: 12 + 24 + 24 for the fat link, 2 for the long link; 198 flops each
+LINK_BUILD_PRODUCTS = 62
 METRIC = "asqtad Dslash HBM GB/s; CG time-to-1e-10 at 20^3x64; solves/s + p99 latency"
 
 LINK_BYTES = {"f64": 144, "f32": 72, "f32r12": 48, "f16r12": 24}
@@ -892,7 +892,7 @@ def run_asqtad(args, asq, torch):
            "config": {"workload": "asqtad_20x20x20x64", "dims": list(dims), "eps": w["eps"]},
            "roofline": {"bound": "alu", "achieved": tf, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
                         "frac": tf / PEAK_FP64_TFLOPS, "traffic": None,
-                        "kernel": "asqtad_build_links: transpose, fat-link and long-link kernels (FP64), "
+                        "kernel": "asqtad_build_links_work: transpose and the three stages (FP64), "
                                   "timed together",
                         "flops_per_call": flops, "ms_per_call": dt * 1e3},
            "solve_mixed32": {"ms": secs * 1e3, "time_to_solution": time_stats(times), "iters": st["iters"],
