@@ -12,8 +12,31 @@
 
 namespace asq {
 
+// Whether a column takes part in a launch.
+__host__ __device__ inline bool state_on(const ColState& s, int mask) {
+  if (mask == MASK_ALL) return true;
+  if (mask == MASK_ACTIVE) return s.active != 0 && s.frozen == 0;
+  return s.active != 0 && s.want_ru != 0;
+}
+
+// alpha of a column inside a launch whose blocks all evaluate state_on on S as they
+// start: false when <p, A p> is not positive and finite.  The block that records
+// leaves what the scalar kernel would have left, except that a breakdown is noted in
+// the status alone: blocks that start later must still find the column on, so the
+// next OP_BETA step takes it out.
+__host__ __device__ inline bool alpha_step(ColState& S, double pAp, bool record, double& alpha) {
+  const bool ok = isfinite(pAp) && pAp > 0;
+  alpha = ok ? S.rr / pAp : 0.0;
+  if (record) {
+    S.pAp = pAp;
+    if (ok) S.alpha = alpha;
+    else S.status = ASQ_ENAN;
+  }
+  return ok;
+}
+
 // Scalar update of one column from its reduced sum s (thread 0 of one block).
-__device__ inline void finalize_column(ColState& S, double s, int op) {
+__host__ __device__ inline void finalize_column(ColState& S, double s, int op) {
   const bool finite = isfinite(s);
   switch (op) {
     case OP_INIT:
@@ -47,6 +70,10 @@ __device__ inline void finalize_column(ColState& S, double s, int op) {
       break;
     case OP_BETA: {
       if (!S.active) break;  // stopped by OP_ALPHA
+      if (S.status == ASQ_ENAN) {  // by alpha_step: s means nothing
+        S.active = 0;
+        break;
+      }
       S.iters += 1;
       S.pbuf ^= 1;  // the new direction becomes current
       if (!finite) {

@@ -16,12 +16,6 @@
 namespace asq {
 namespace {
 
-__device__ __forceinline__ bool state_on(const ColState& s, int mask) {
-  if (mask == MASK_ALL) return true;
-  if (mask == MASK_ACTIVE) return s.active != 0 && s.frozen == 0;
-  return s.active != 0 && s.want_ru != 0;
-}
-
 template <class R>
 __device__ __forceinline__ Vec3<R> zero3() {
   Vec3<R> v;

@@ -38,9 +38,7 @@ namespace {
 __device__ __forceinline__ bool col_on(const DslashArgs& A, int c) {
   if (c >= A.ncol) return false;
   if (A.mask == MASK_ALL || A.st == nullptr) return true;
-  const ColState& s = A.st[c];
-  if (A.mask == MASK_ACTIVE) return s.active != 0 && s.frozen == 0;
-  return s.active != 0 && s.want_ru != 0;
+  return state_on(A.st[c], A.mask);
 }
 
 // Raw neighbour record of one column: FP16 keeps the 16-byte record (halves and
@@ -254,26 +252,13 @@ __device__ __forceinline__ void pipe_run(const DslashArgs& A, int i, const Site&
   if constexpr (K + 1 < 16) pipe_run<Link, InT, R, K + 1, LDS>(A, i, s, on, col, in, win, st, acc);
 }
 
-// alpha of column c from its reduced |p|^2 and |t|^2 partial sums: false (and
-// the column stopped, by one block) when <p, A p> is not positive and finite.
-// Block 0 also leaves the record the scalar kernel would have left; no block of
-// the launch reads those fields.
+// alpha of column c from its reduced |p|^2 and |t|^2 partial sums: false when
+// <p, A p> is not positive and finite.  Block 0 records it; no block of the launch
+// reads the fields that it writes (see alpha_step).
 __device__ __forceinline__ bool fold_alpha(const DslashArgs& A, int c, int sblk, double pp, double tt,
                                            double& alpha) {
   ColState& S = A.st[c];
-  const double pAp = S.a * pp + tt;
-  const bool ok = isfinite(pAp) && pAp > 0;
-  alpha = ok ? S.rr / pAp : 0.0;
-  if (sblk == 0 && threadIdx.x == 0) {
-    S.pAp = pAp;
-    if (ok) {
-      S.alpha = alpha;
-    } else {
-      S.status = ASQ_ENAN;
-      S.active = 0;
-    }
-  }
-  return ok;
+  return alpha_step(S, S.a * pp + tt, sblk == 0 && threadIdx.x == 0, alpha);
 }
 
 // The column's new direction buffer (pbuf == 0: the alternate one).
@@ -398,7 +383,7 @@ __global__ void __launch_bounds__(kBlock) dslash_kernel(const DslashArgs A) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           alpha[r] = 0;
-          if (!on[r]) continue;  // uniform over the block
+          if (!on[r]) continue;  // uniform over the block (the launch changes nothing that col_on reads)
           double pp = 0, tt = 0;
 #pragma unroll
           for (int q = 0; q < 4; ++q)
@@ -644,7 +629,7 @@ __global__ void __launch_bounds__(4 * kSplitSites) dslash_split_kernel(const Dsl
   const int mu = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kSplitSites);
   const int lane = (int)threadIdx.x % kSplitSites;
   const bool lead = mu == 0;
-  if (!col_on(A, c)) return;  // uniform over the block
+  if (!col_on(A, c)) return;  // uniform over the block, as in dslash_kernel
   const void* in = A.in_sel ? pick_new(A, A.in, A.in_alt, c) : A.in;
   const int i = sub * kSplitSites + lane;
   const bool valid = i < A.g.half;

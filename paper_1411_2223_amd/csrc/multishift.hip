@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(kBlock) beta_shift_kernel(ColState* st, const 
                                                             int nsh) {
   const int c = blockIdx.x;
   ColState& S = st[c];
-  if (S.active != 0 && S.frozen == 0) {  // uniform over the block
+  if (state_on(S, MASK_ACTIVE)) {  // uniform over the block
     __shared__ double part[kBlock / 64];
     const double s = block_sum(strided_sum<SUB>(pr + (size_t)c * nblk * SUB, nblk), part);
     if (threadIdx.x == 0) finalize_column(S, s, OP_BETA);

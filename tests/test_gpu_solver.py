@@ -611,3 +611,31 @@ def test_multishift_with_split_form_is_bitwise_the_plain_form(asq, monkeypatch, 
     assert want.rc == 0 and got.rc == 0
     assert got.x.cpu().numpy().tobytes() == want.x.cpu().numpy().tobytes()
     assert [s["iters"] for s in got.stats] == [s["iters"] for s in want.stats]
+
+
+@pytest.mark.parametrize("mode", ["f64", "mixed32", "mixed16"])
+@pytest.mark.parametrize("form", ["tiles of two", "tiles of three", "split"])
+def test_breakdown_leaves_the_other_columns_alone(asq, monkeypatch, mode, form):
+    """A column whose first <p, A p> overflows stops with ASQ_ENAN; the columns of its tile keep the bits
+    of a batch in which it is healthy.  16^3 x 64 has 512 site blocks, more than start together, and
+    alpha is formed inside D_eo."""
+    if form == "tiles of three" and mode == "f64":
+        pytest.skip("no three-column tile for FP64 vectors")
+    dims, masses = (16, 16, 16, 64), [0.2, 0.3, 0.4]
+    fat, lng = gauge_arrays(dims, 0.3, 6)
+    g = asq.Gauge(dims, fat, lng, precs=("f64", "f32"), recon=18)
+    code = {"tiles of two": asq.variant_code(2, True, 0), "tiles of three": asq.variant_code(6, True, 0) | 1 << 9,
+            "split": 1 | 1 << 10}[form]
+    monkeypatch.setenv("ASQ_TUNE", "0")
+    monkeypatch.setenv("ASQ_VARIANT", str(code))
+    b = synth.make_sources(dims, 3, 97)
+    xw, want = _solve(asq, g, masses, b, mode)
+    assert want.rc == 0
+    # |b|^2 is finite, but p overflows FP32, or |D p|^2 overflows FP64
+    b[0] *= 1e39 if mode != "f64" else np.sqrt(1e308 / np.vdot(b[0], b[0]).real)
+    print(f"breakdown {mode} {form}", flush=True)
+    x, res = _solve(asq, g, masses, b, mode)
+    assert res.rc == asq.ASQ_ENAN and res.stats[0]["status"] == asq.ASQ_ENAN and res.stats[0]["iters"] == 0
+    for c in (1, 2):
+        assert res.stats[c]["status"] == 0 and res.stats[c]["iters"] == want.stats[c]["iters"]
+        assert x[c].tobytes() == xw[c].tobytes()
