@@ -387,6 +387,26 @@ static HostRes& host_res() {
   return r;
 }
 
+// What a solve has enqueued.  However the call returns, it has drained by then: the
+// work writes the caller's x and workspace, and copies states into the pinned mirror
+// that the thread's next solve starts from.
+struct InFlight {
+  hipStream_t s;
+  hipGraphExec_t exec = nullptr;
+  bool busy = true;
+  explicit InFlight(hipStream_t s_) : s(s_) {}
+  InFlight(const InFlight&) = delete;
+  InFlight& operator=(const InFlight&) = delete;
+  hipError_t drain() {
+    const hipError_t e = busy ? hipStreamSynchronize(s) : hipSuccess;
+    busy = false;
+    if (exec) (void)hipGraphExecDestroy(exec);
+    exec = nullptr;
+    return e;
+  }
+  ~InFlight() { (void)drain(); }
+};
+
 int capture_block(const Batch& B, int iters, hipStream_t cap, hipGraphExec_t* exec) {
   hipGraph_t graph = nullptr;
   ASQ_HIP_TRY(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
@@ -518,13 +538,13 @@ int asq::solve_batch(const asq_gauge* g, int nrhs, const double* masses, const d
   ColState* mirror[2] = {H.pinned, H.pinned + nrhs};
   init_states(B, masses, params, mirror[0], tols);
   set_stall(mirror[0], nrhs, params->mode);
+  InFlight flight(s);
   ASQ_HIP_TRY(hipMemcpyAsync(B.st, mirror[0], nrhs * sizeof(ColState), hipMemcpyHostToDevice, s));
   if ((rc = guess ? enqueue_init_guess(B, s) : enqueue_init(B, 0, nrhs, s))) return rc;
   // the mirror is reused below: make sure the upload has consumed it
   ASQ_HIP_TRY(hipStreamSynchronize(s));
 
   const int poll = params->poll_iters > 0 ? params->poll_iters : 8;
-  hipGraphExec_t exec = nullptr;
   int slot = 0, pending = -1, last = -1;
   long blocks = 0;
   const long max_blocks = (long)params->maxiter / poll + 4;
@@ -532,14 +552,9 @@ int asq::solve_batch(const asq_gauge* g, int nrhs, const double* masses, const d
   for (;;) {
     // the first block is enqueued launch by launch, and the graph captured while the
     // GPU works on it
-    if (params->use_graph && blocks == 1 && (rc = capture_block(B, poll, H.cap, &exec))) return rc;
-    if (exec) {
-      hipError_t e = hipGraphLaunch(exec, s);
-      if (e != hipSuccess) {
-        (void)hipGraphExecDestroy(exec);
-        set_last_error(hipGetErrorString(e));
-        return ASQ_EHIP;
-      }
+    if (params->use_graph && blocks == 1 && (rc = capture_block(B, poll, H.cap, &flight.exec))) return rc;
+    if (flight.exec) {
+      ASQ_HIP_TRY(hipGraphLaunch(flight.exec, s));
     } else if ((rc = enqueue_block(B, poll, s))) {
       return rc;
     }
@@ -570,8 +585,7 @@ int asq::solve_batch(const asq_gauge* g, int nrhs, const double* masses, const d
     pending = slot;
     slot ^= 1;
   }
-  ASQ_HIP_TRY(hipStreamSynchronize(s));
-  if (exec) (void)hipGraphExecDestroy(exec);
+  ASQ_HIP_TRY(flight.drain());
   int worst = ASQ_OK;
   const ColState* fin = mirror[last];
   std::vector<int> esc;
