@@ -20,7 +20,10 @@
 //      the pairs are dealt to threads in order of distance, so the lanes of a
 //      wave share a round;
 //   3. X_AD = G1(A)^dag U_AD G4(D) and Y_AD = G3(A)^dag U_AD G2(D) to LDS;
-//   4. the contraction (contract): operators that pair up share their products.
+//   4. the contraction: a lane owns one operator and one corner A, sums the 16
+//      terms D and accumulates all 81 outputs; the 16 corners' partial sums of
+//      an operator are added across lanes by halving exchanges, after which
+//      each lane stores the outputs it ended with.
 #include <math.h>
 #include <string.h>
 
@@ -33,8 +36,7 @@ namespace {
 
 constexpr int kNprThreads = 256;
 constexpr int kNprOpsPerLaunch = 32;
-constexpr int kNprOpsPerPass = 16;    // 4 per wave, each over the 16 lanes of its corners A
-constexpr int kNprPairsPerPass = 8;   // 2 per wave, each over 32 lanes: corners A and halves of D
+constexpr int kNprOpsPerPass = 16;  // 4 per wave, each over the 16 lanes of its corners A
 // a matrix per pair (A, D) at A * kRow + 9 D complex entries: one spare entry per
 // row A puts the 16 rows A that a wave reads at once in different LDS banks
 constexpr int kRow = 16 * 9 + 1;
@@ -60,12 +62,7 @@ struct NprOp {
   unsigned char p1, p2;  // S1 ^ F1, S2 ^ F2: B = A ^ p1, D = C ^ p2
   unsigned short neg1;   // bit A: M1_{A, A^p1} eps(z_A) = -1 (else +1)
   unsigned short neg2;   // bit C: M2_{C, C^p2} eps(z_C) = -1
-  unsigned char out;     // place of the operator in the launch's output
-  // of a pair (see contract): the partner's place, and the signs lambda and kappa
-  unsigned char out_b;
-  unsigned char lambda_neg, kappa_neg;
 };
-constexpr unsigned char kNoPartner = 255;  // out_b of an operator summed by the pair form on its own
 
 struct NprArgs {
   int X, Y, Z, T;
@@ -75,8 +72,7 @@ struct NprArgs {
   double2* out;     // [nop_total][nz][81]
   long nz;
   int op0;          // index of this launch's first operator in the output
-  int nsingle;      // operators on their own: ops[0 .. nsingle)
-  int npair;        // pairs: ops[nsingle .. nsingle + npair)
+  int nop;
   NprOp ops[kNprOpsPerLaunch];
 };
 
@@ -138,160 +134,6 @@ __device__ __forceinline__ void m3mul_bdag(const c64* a, const c64* b, c64* c) {
       s = cmac_cj(s, b[3 * j + 2], a[3 * i + 2]);
       c[3 * i + j] = s;
     }
-}
-
-// Contraction over the pairs (A, D) of one hypercube.  With C = D ^ p2 and B = A ^ p1,
-//   V[a1][a2][a3][a4] = sum_{A,D} f(A, D) X_AD[a1][a4] Y_CB[a3][a2],  f = s1(A) s2(C).
-// A lane owns one operator and one corner A, sums D one a3 at a time (27 outputs) and
-// shares the sums with the other lanes of the operator by halving exchanges, after
-// which each lane stores the outputs it ended with.  The 16 lanes of an operator read
-// 16 rows A of X and 16 entries B of a row C of Y, each in its own LDS banks.
-//
-// PAIR: two operators a, b with p1_b = p1_a ^ 1, p2_b = p2_a ^ 1 and f_b = kappa f_a
-// (a spin structure and its product with gamma_x on both bilinears), where
-// f_a(A ^ 1, D ^ 1) = lambda f_a(A, D), are summed together over the reps (A even):
-//   V_a = sum f (X Y + lambda X1 Y1),  kappa V_b = sum f (X Y1 + lambda X1 Y),
-// X1, Y1 the entries at flipped x bits.  With X+- = X +- X1 (Y alike) and
-//   S0 = sum f X+ Y(lambda),  S1 = sum f X- Y(-lambda),
-// V_a = (S0 + S1) / 2 and kappa V_b = lambda (S0 - S1) / 2: two operators for the
-// products of one.  X and Y hold the sums (even A, even B) and differences; lanes of
-// even A form S0, of odd A S1; 32 lanes per pair, each with half of the D.  16
-// operators of 20^3 x 64 (8 pairs) take 1.87 ms, 2.50 ms one by one (before the lane
-// swaps of the exchanges, 1.98).
-// DPP controls: the lane 8 on in its row of 16 (lane ^ 8), and lane ^ 2
-constexpr int kRowRotate8 = 0x128, kQuadXor2 = 0x4e;
-template <int CTRL>
-__device__ __forceinline__ double from_lane(double x) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
-  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, 0xf, 0xf, false);
-  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, false);
-  return __longlong_as_double((long long)((unsigned long long)hi << 32 | lo));
-}
-// One halving step over lane bit BIT (32 or 16): lo of this lane and its partner where
-// the bit is clear, hi of both where it is set.  The swap exchanges the upper half
-// (odd rows) of one register with the lower half (even rows) of the other.
-template <int BIT>
-__device__ __forceinline__ double add_swapped(double lo, double hi) {
-  const unsigned long long a = (unsigned long long)__double_as_longlong(lo);
-  const unsigned long long b = (unsigned long long)__double_as_longlong(hi);
-  auto swap = [](unsigned x, unsigned y) {
-    if constexpr (BIT == 32) return __builtin_amdgcn_permlane32_swap(x, y, false, false);
-    else return __builtin_amdgcn_permlane16_swap(x, y, false, false);
-  };
-  const auto l = swap((unsigned)a, (unsigned)b);
-  const auto h = swap((unsigned)(a >> 32), (unsigned)(b >> 32));
-  return __longlong_as_double((long long)((unsigned long long)h[0] << 32 | l[0])) +
-         __longlong_as_double((long long)((unsigned long long)h[1] << 32 | l[1]));
-}
-
-template <bool PAIR>
-__device__ __forceinline__ void contract(const NprArgs& P, long z, const c64* Xs, const c64* Ys) {
-  const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
-  constexpr int kLanes = PAIR ? 32 : 16, kPass = PAIR ? kNprPairsPerPass : kNprOpsPerPass;
-  constexpr int kSum = PAIR ? 8 : 16;  // D per lane
-  const int n = PAIR ? P.npair : P.nsingle;
-  // the lane bits that are summed over (of A, and of D in a pair) are the upper four,
-  // for the exchanges below; then, in a pair, the lowest bit of A; then the operator
-  const int Ak = PAIR ? lane >> 1 & 15 : lane >> 2, t = PAIR ? Ak & 1 : 0;
-  const int d0 = PAIR ? (lane >> 5) * kSum : 0;
-  const c64* xrow = Xs + Ak * kRow;
-  for (int pass = 0; pass * kPass < n; ++pass) {
-    const int opl = pass * kPass + (64 / kLanes) * wv + lane % (64 / kLanes);
-    const bool act = opl < n;
-    NprOp o = {};
-    if (act) o = P.ops[(PAIR ? P.nsingle : 0) + opl];
-    const int Ar = Ak ^ t;  // the rep's corner
-    const double s1 = (o.neg1 >> Ar & 1) ? -1.0 : 1.0;
-    int B = Ar ^ o.p1, p2 = o.p2;
-    double sy = s1;
-    if constexpr (PAIR) {
-      // Y(+-) of the pair of (C, B): at the entry whose second index is even, or the
-      // next one; a difference taken from its other end changes sign
-      const int b0 = B & 1, ty = t ^ o.lambda_neg;
-      p2 ^= b0;
-      B = (B ^ b0) | ty;
-      if (b0 & ty) sy = -sy;
-    }
-    const c64* ycol = Ys + 9 * B;
-    double* const out =
-        (double*)(P.out + ((size_t)(P.op0 + (act ? (t ? o.out_b : o.out) : 0)) * P.nz + z) * 81);
-#pragma unroll 1
-    for (int a3 = 0; a3 < 3; ++a3) {
-      double v[54];  // [a1][a2][a4] as (re, im) pairs
-#pragma unroll
-      for (int k = 0; k < 54; ++k) v[k] = 0.0;
-      if (act) {
-        const c64* ybase = ycol + 3 * a3;
-#pragma unroll 2
-        for (int k = 0; k < kSum; ++k) {
-          const int Dk = d0 + k;
-          const double s = (o.neg2 >> (Dk ^ o.p2) & 1) ? -sy : sy;
-          c64 xv[9], yv[3];
-#pragma unroll
-          for (int e = 0; e < 9; ++e) xv[e] = xrow[9 * Dk + e];  // X_AD[a1][a4]
-#pragma unroll
-          for (int e = 0; e < 3; ++e) {                           // Y_CB[a3][a2]
-            const c64 y = ybase[(Dk ^ p2) * kRow + e];
-            yv[e] = make_double2(s * y.x, s * y.y);
-          }
-#pragma unroll
-          for (int a1 = 0; a1 < 3; ++a1)
-#pragma unroll
-            for (int a2 = 0; a2 < 3; ++a2)
-#pragma unroll
-              for (int a4 = 0; a4 < 3; ++a4) {
-                const int q = 2 * (9 * a1 + 3 * a2 + a4);
-                const c64 a = xv[3 * a1 + a4], b = yv[a2];
-                v[q] = __builtin_fma(a.x, b.x, v[q]);
-                v[q] = __builtin_fma(-a.y, b.y, v[q]);
-                v[q + 1] = __builtin_fma(a.x, b.y, v[q + 1]);
-                v[q + 1] = __builtin_fma(a.y, b.x, v[q + 1]);
-              }
-        }
-      }
-      // 16 lanes add their partial sums by halving: at each step a lane keeps the
-      // lower or upper part of its current range (by one lane bit), adds the partner's
-      // copy of that part and hands over the other part.  Ranges 54 -> 27 -> 14 -> 7 ->
-      // 4 (odd lengths padded by a zero).  The long steps are lane swaps and a row
-      // rotation, which leave the LDS pipe to the operands.
-      const bool u3 = lane & 32, u2 = lane & 16, u1 = lane & 8, u0 = lane & 4;
-#pragma unroll
-      for (int k = 0; k < 27; ++k) v[k] = add_swapped<32>(v[k], v[k + 27]);
-#pragma unroll
-      for (int k = 0; k < 14; ++k) v[k] = add_swapped<16>(v[k], k + 14 < 27 ? v[k + 14] : 0.0);
-#pragma unroll
-      for (int k = 0; k < 7; ++k) {
-        const double lo = v[k], hi = k + 7 < 14 ? v[k + 7] : 0.0;
-        v[k] = (u1 ? hi : lo) + from_lane<kRowRotate8>(u1 ? lo : hi);
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const double lo = v[k], hi = k + 4 < 7 ? v[k + 4] : 0.0;
-        v[k] = (u0 ? hi : lo) + __shfl_xor(u0 ? lo : hi, 4, 64);
-      }
-      if constexpr (PAIR) {
-        // lanes of even and odd A hold S0 and S1 of the same outputs
-        const double h = t && (o.lambda_neg != o.kappa_neg) ? -0.5 : 0.5;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const double w = from_lane<kQuadXor2>(v[k]);
-          v[k] = h * (t ? w - v[k] : v[k] + w);
-        }
-      }
-      if (act && !(t && o.out_b == kNoPartner)) {
-        // this lane's 4 entries start at 27 u3 + 14 u2 + 7 u1 + 4 u0 of the 54;
-        // an entry is real where it lies inside every range it was cut from
-        const int o3 = 4 * u0, o2 = 7 * u1 + o3, o1 = 14 * u2 + o2, base = 27 * u3 + o1;
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (o3 + k < 7 && o2 + k < 14 && o1 + k < 27) {
-            const int q = base + k, jj = q >> 1;  // jj = 9 a1 + 3 a2 + a4
-            const int a1 = jj / 9, a2 = jj / 3 % 3, a4 = jj % 3;
-            out[2 * (27 * a1 + 9 * a2 + 3 * a3 + a4) + (q & 1)] = v[k];
-          }
-      }
-    }
-  }
 }
 
 __global__ void __launch_bounds__(kNprThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) npr_kernel(const NprArgs P) {
@@ -385,50 +227,114 @@ __global__ void __launch_bounds__(kNprThreads) __attribute__((amdgpu_waves_per_e
   }
   __syncthreads();
   // 3. the bilinears' colour matrices of the pair (A, D)
+  c64 xm[9], ym[9];
   {
-    c64 xm[9], ym[9], t[9];
+    c64 t[9];
     m3mul_dag(Gs + (0 * 16 + A) * 9, u, t);  // G1(A)^dag U_AD
     m3mul(t, Gs + (3 * 16 + D) * 9, xm);    // ... G4(D)
     m3mul_dag(Gs + (2 * 16 + A) * 9, u, t);  // G3(A)^dag U_AD
     m3mul(t, Gs + (1 * 16 + D) * 9, ym);    // ... G2(D)
-    __syncthreads();  // everyone is done with the propagators, steps and U in LDS
+  }
+  __syncthreads();  // everyone is done with the propagators, steps and U in LDS
 #pragma unroll
-    for (int e = 0; e < 9; ++e) {
-      Xs[A * kRow + 9 * D + e] = xm[e];
-      Ys[A * kRow + 9 * D + e] = ym[e];
-    }
+  for (int e = 0; e < 9; ++e) {
+    Xs[A * kRow + 9 * D + e] = xm[e];
+    Ys[A * kRow + 9 * D + e] = ym[e];
   }
   __syncthreads();
-  // 4. contraction of the operators on their own, then of the pairs on the sums and
-  //    differences
-  contract<false>(P, z, Xs, Ys);
-  if (P.npair > 0) {
-    __syncthreads();  // everyone is done with X and Y
-    {
-      // X+ of the rep (A even, D) at (A, D), X- at (A + 1, D): the thread of (A, D) with
-      // A odd belongs to the rep (A - 1, D ^ 1).  Y+ and Y- likewise, by the parity of
-      // the second index.
-      const int t = A & 1, s = D & 1;
-      const int own = A * kRow + 9 * D, other = (A ^ 1) * kRow + 9 * (D ^ 1);
-      const double ft = t ? -1.0 : 1.0, fs = s ? -1.0 : 1.0;
-      c64 xm[9], ym[9];
+  // 4. contraction.  Lane l of wave w takes operator 4 w + (l >> 4) of the pass
+  //    and corner A = l & 15.  With C = D ^ p2 and B = A ^ p1 it sums, over D,
+  //    sign * X_AD[a1][a4] Y_CB[a3][a2] into out[a1][a2][a3][a4], one a3 at a
+  //    time (27 outputs).  The 16 lanes of an operator read 16 rows A of X and
+  //    16 entries B of a row C of Y, each in its own LDS banks.
+  //    Each operator is summed on its own.  Two that differ by an x flip of both
+  //    bilinears can share products through sums and differences of their terms (1.82
+  //    instead of 2.49 ms for 16 operators at 20^3 x 64), but then the smaller of the two
+  //    gets the rounding of the larger, and propagators differ in size between corners.
+  const int lane = tid & 63, wv = tid >> 6;
+  const int Ak = lane & 15;
+  for (int pass = 0; pass * kNprOpsPerPass < P.nop; ++pass) {
+    const int opl = pass * kNprOpsPerPass + 4 * wv + (lane >> 4);
+    const bool act = opl < P.nop;
+    NprOp o = {0, 0, 0, 0};
+    if (act) o = P.ops[opl];
+    const int B = Ak ^ o.p1;
+    const double s1 = (o.neg1 >> Ak & 1) ? -1.0 : 1.0;
+    const c64* xrow = Xs + Ak * kRow;
+    double* const out = (double*)(P.out + ((size_t)(P.op0 + (act ? opl : 0)) * P.nz + z) * 81);
+#pragma unroll 1
+    for (int a3 = 0; a3 < 3; ++a3) {
+      double v[54];  // [a1][a2][a4] as (re, im) pairs
 #pragma unroll
-      for (int e = 0; e < 9; ++e) {
-        const c64 x = Xs[other + e], y = Ys[other + e], x0 = Xs[own + e], y0 = Ys[own + e];
-        xm[e] = make_double2(x.x + ft * x0.x, x.y + ft * x0.y);
-        ym[e] = make_double2(y.x + fs * y0.x, y.y + fs * y0.y);
+      for (int k = 0; k < 54; ++k) v[k] = 0.0;
+      if (act) {
+        const c64* ybase = Ys + 9 * B + 3 * a3;
+#pragma unroll 2
+        for (int Dk = 0; Dk < 16; ++Dk) {
+          const int C = Dk ^ o.p2;
+          const double s = (o.neg2 >> C & 1) ? -s1 : s1;
+          c64 xv[9], yv[3];
+#pragma unroll
+          for (int e = 0; e < 9; ++e) xv[e] = xrow[9 * Dk + e];  // X_AD[a1][a4]
+#pragma unroll
+          for (int e = 0; e < 3; ++e) {                           // Y_CB[a3][a2]
+            const c64 y = ybase[C * kRow + e];
+            yv[e] = make_double2(s * y.x, s * y.y);
+          }
+#pragma unroll
+          for (int a1 = 0; a1 < 3; ++a1)
+#pragma unroll
+            for (int a2 = 0; a2 < 3; ++a2)
+#pragma unroll
+              for (int a4 = 0; a4 < 3; ++a4) {
+                const int k = 2 * (9 * a1 + 3 * a2 + a4);
+                const c64 a = xv[3 * a1 + a4], b = yv[a2];
+                v[k] = __builtin_fma(a.x, b.x, v[k]);
+                v[k] = __builtin_fma(-a.y, b.y, v[k]);
+                v[k + 1] = __builtin_fma(a.x, b.y, v[k + 1]);
+                v[k + 1] = __builtin_fma(a.y, b.x, v[k + 1]);
+              }
+        }
       }
-      __syncthreads();
-      c64* xd = Xs + A * kRow + 9 * (D ^ t);
-      c64* yd = Ys + (A ^ s) * kRow + 9 * D;
+      // the 16 lanes of an operator (lane bits 0..3) add their partial sums by
+      // halving: at each step a lane keeps the lower or upper part of its current
+      // range (by one lane bit), adds the partner's copy of that part and hands
+      // over the other part.  Ranges 54 -> 27 -> 14 -> 7 -> 4 (odd lengths padded
+      // by a zero).
+      const bool u3 = lane & 8, u2 = lane & 4, u1 = lane & 2, u0 = lane & 1;
 #pragma unroll
-      for (int e = 0; e < 9; ++e) {
-        xd[e] = xm[e];
-        yd[e] = ym[e];
+      for (int k = 0; k < 27; ++k) {
+        const double lo = v[k], hi = v[k + 27];
+        v[k] = (u3 ? hi : lo) + __shfl_xor(u3 ? lo : hi, 8, 64);
+      }
+#pragma unroll
+      for (int k = 0; k < 14; ++k) {
+        const double lo = v[k], hi = k + 14 < 27 ? v[k + 14] : 0.0;
+        v[k] = (u2 ? hi : lo) + __shfl_xor(u2 ? lo : hi, 4, 64);
+      }
+#pragma unroll
+      for (int k = 0; k < 7; ++k) {
+        const double lo = v[k], hi = k + 7 < 14 ? v[k + 7] : 0.0;
+        v[k] = (u1 ? hi : lo) + __shfl_xor(u1 ? lo : hi, 2, 64);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const double lo = v[k], hi = k + 4 < 7 ? v[k + 4] : 0.0;
+        v[k] = (u0 ? hi : lo) + __shfl_xor(u0 ? lo : hi, 1, 64);
+      }
+      if (act) {
+        // this lane's 4 entries start at 27 u3 + 14 u2 + 7 u1 + 4 u0 of the 54;
+        // an entry is real where it lies inside every range it was cut from
+        const int o3 = 4 * u0, o2 = 7 * u1 + o3, o1 = 14 * u2 + o2, base = 27 * u3 + o1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (o3 + k < 7 && o2 + k < 14 && o1 + k < 27) {
+            const int q = base + k, jj = q >> 1;  // jj = 9 a1 + 3 a2 + a4
+            const int a1 = jj / 9, a2 = jj / 3 % 3, a4 = jj % 3;
+            out[2 * (27 * a1 + 9 * a2 + 3 * a3 + a4) + (q & 1)] = v[k];
+          }
       }
     }
-    __syncthreads();
-    contract<true>(P, z, Xs, Ys);
   }
 }
 
@@ -445,29 +351,6 @@ int rev(int X) {
   const int k = __builtin_popcount(X);
   return ((k * (k - 1) / 2) & 1) ? -1 : 1;
 }
-int bit(unsigned short m, int k) { return m >> k & 1; }
-
-// f_a(A ^ 1, D ^ 1) / f_a(A, D): sets lambda if it is constant, as the pair form needs.
-bool set_lambda(NprOp& a) {
-  const int l1 = bit(a.neg1, 0) ^ bit(a.neg1, 1), l2 = bit(a.neg2, a.p2) ^ bit(a.neg2, 1 ^ a.p2);
-  for (int k = 0; k < 16; ++k)
-    if ((bit(a.neg1, k) ^ bit(a.neg1, k ^ 1)) != l1 || (bit(a.neg2, k ^ a.p2) ^ bit(a.neg2, k ^ 1 ^ a.p2)) != l2)
-      return false;
-  a.lambda_neg = (unsigned char)(l1 ^ l2);
-  return true;
-}
-
-// Whether b is the partner of a (see contract): f_b / f_a is constant.  Sets kappa.
-bool set_partner(NprOp& a, const NprOp& b) {
-  if (b.p1 != (a.p1 ^ 1) || b.p2 != (a.p2 ^ 1)) return false;
-  const int k1 = bit(a.neg1, 0) ^ bit(b.neg1, 0), k2 = bit(a.neg2, a.p2) ^ bit(b.neg2, b.p2);
-  for (int k = 0; k < 16; ++k)
-    if ((bit(a.neg1, k) ^ bit(b.neg1, k)) != k1 || (bit(a.neg2, k ^ a.p2) ^ bit(b.neg2, k ^ b.p2)) != k2) return false;
-  a.kappa_neg = (unsigned char)(k1 ^ k2);
-  a.out_b = b.out;
-  return true;
-}
-
 // (1/4) Tr[gamma_A^dag gamma_S gamma_B gamma_F^dag] for B = A ^ S ^ F (the only
 // nonzero entry of row A): the product is r(A) r(F) gamma_A gamma_S gamma_B gamma_F,
 // which reduces to a sign times gamma_0 = 1.
@@ -542,54 +425,19 @@ extern "C" int asqtad_npr_fourfermion(const int dims[4], const double* thin_dev,
   hipStream_t s = (hipStream_t)hip_stream;
   for (int op0 = 0; op0 < nop; op0 += kNprOpsPerLaunch) {
     P.op0 = op0;
-    const int n = nop - op0 < kNprOpsPerLaunch ? nop - op0 : kNprOpsPerLaunch;
-    NprOp all[kNprOpsPerLaunch];
-    for (int k = 0; k < n; ++k) {
+    P.nop = nop - op0 < kNprOpsPerLaunch ? nop - op0 : kNprOpsPerLaunch;
+    for (int k = 0; k < P.nop; ++k) {
       const int* o = ops_host + 4 * (op0 + k);
-      NprOp& q = all[k];
-      q = NprOp{};
+      NprOp& q = P.ops[k];
       q.p1 = (unsigned char)(o[0] ^ o[1]);
       q.p2 = (unsigned char)(o[2] ^ o[3]);
-      q.out = (unsigned char)k;
+      q.neg1 = q.neg2 = 0;
       for (int A = 0; A < 16; ++A) {
         // eps(z_A) = (-1)^|A|: the hypercube origin 2z has even coordinates
         const int eps = (__builtin_popcount(A) & 1) ? -1 : 1;
         if (spin_taste_sign(A, o[0], o[1]) * eps < 0) q.neg1 |= (unsigned short)(1u << A);
         if (spin_taste_sign(A, o[2], o[3]) * eps < 0) q.neg2 |= (unsigned short)(1u << A);
       }
-    }
-    // Each operator joins the first later one that is its partner.  The pair form
-    // sums an operator without a partner in a slot of its own, for what it costs in
-    // the single form plus half an exchange.
-    NprOp slots[kNprOpsPerLaunch], rest[kNprOpsPerLaunch];
-    bool used[kNprOpsPerLaunch] = {};
-    int ns = 0, npair = 0, nrest = 0;
-    for (int k = 0; k < n; ++k) {
-      if (used[k]) continue;
-      NprOp a = all[k];
-      a.out_b = kNoPartner;
-      if (!set_lambda(a)) {
-        rest[nrest++] = a;
-        continue;
-      }
-      for (int j = k + 1; j < n; ++j)
-        if (!used[j] && set_partner(a, all[j])) {
-          used[j] = true;
-          ++npair;
-          break;
-        }
-      slots[ns++] = a;
-    }
-    // a pass of 8 slots of the pair form takes 0.6 of one of 16 operators of the single
-    // form (half the products, the same exchanges)
-    const int by_slots = 6 * ((ns + kNprPairsPerPass - 1) / kNprPairsPerPass);
-    const int by_ops = 10 * ((ns + npair + kNprOpsPerPass - 1) / kNprOpsPerPass);
-    P.nsingle = P.npair = 0;
-    if (by_slots < by_ops) {
-      for (int k = 0; k < nrest; ++k) P.ops[P.nsingle++] = rest[k];
-      for (int k = 0; k < ns; ++k) P.ops[P.nsingle + P.npair++] = slots[k];
-    } else {
-      for (int k = 0; k < n; ++k) P.ops[P.nsingle++] = all[k];
     }
     npr_kernel<<<(unsigned)nz, kNprThreads, 0, s>>>(P);
     ASQ_HIP_TRY(hipGetLastError());

@@ -167,3 +167,47 @@ def test_npr_paired_operators(asq, label):
     G = random_props(dims, 29)
     ops = _op_lists()[label]
     compare(run_gpu(asq, dims, U, G, ops), oracle.npr_fourfermion(dims, U, G, ops), label)
+
+
+def _graded_props(dims, seed, e):
+    """Random propagators whose odd sites are scaled by e."""
+    X, Y, Z, T = dims
+    x = np.arange(int(np.prod(dims)))
+    odd = (x % X + x // X % Y + x // (X * Y) % Z + x // (X * Y * Z)) & 1
+    return [g * np.where(odd, e, 1.0)[:, None, None] for g in random_props(dims, seed)]
+
+
+# eight pairs of operators that differ by gamma_x on both bilinears, so one of even and one of odd
+# spin-taste parity each; and the same with other operators among them
+@pytest.mark.parametrize("e", [1.0, 0.1, 1e-2, 1e-4])
+@pytest.mark.parametrize("label", ["nine slots", "mixed, 29"])
+def test_npr_accuracy_per_operator(asq, label, e):
+    """Staggered propagators differ in size between the parities, and with them the operators: every
+    operator is accurate relative to its own largest entry.  An entry sums 256 products whose
+    roundings, a few 1e-16 of a product each, add up as a random walk, like the products
+    themselves: 1e-14 of the largest entry leaves a factor of ten."""
+    dims = (4, 4, 4, 4)
+    U = synth.thin_links(dims, 0.5, 30).reshape(256, 4, 3, 3)
+    G = _graded_props(dims, 31, e)
+    ops = _op_lists()[label]
+    got, want = run_gpu(asq, dims, U, G, ops), oracle.npr_fourfermion(dims, U, G, ops)
+    err = [np.abs(got[k] - want[k]).max() / np.abs(want[k]).max() for k in range(len(ops))]
+    print(f"graded by {e} {label}: largest error {max(err):.2e} of an operator's largest entry", flush=True)
+    assert max(err) <= 1e-14
+
+
+def test_npr_operator_does_not_depend_on_the_list(asq):
+    """An operator has the same bits alone and among others, and is exactly zero where every product is."""
+    dims = (4, 4, 4, 4)
+    U = synth.thin_links(dims, 0.5, 32).reshape(256, 4, 3, 3)
+    for e in (1.0, 0.0):
+        G = _graded_props(dims, 33, e)
+        for label in ("nine slots", "mixed, 29", "two launches"):
+            ops = _op_lists()[label]
+            got = run_gpu(asq, dims, U, G, ops)
+            for k, op in enumerate(ops):
+                print(f"list {label} e={e} op {k}", flush=True)
+                assert np.array_equal(run_gpu(asq, dims, U, G, [op])[0], got[k])
+                odd = any(bin(op[j] ^ op[j + 1]).count("1") & 1 for j in (0, 2))
+                if e == 0.0 and odd:  # each product holds a propagator of an odd site
+                    assert not np.any(got[k])
