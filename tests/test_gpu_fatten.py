@@ -219,3 +219,61 @@ def test_plaquette_kernels_match_torch(asq, dims):
             scale += float(tr.abs().sum())
     got = asq.plaquette(dims, thin)
     assert abs(got - want / (6 * X * Y * Z * T)) <= 1e-13 * scale / (6 * X * Y * Z * T)
+
+
+def _free_form(asq, dims, thin, u0):
+    rc, fat, lng = _links_by(asq, dims, thin, u0, None)
+    assert rc == 0
+    return fat, lng
+
+
+@pytest.mark.parametrize("side", [False, True])
+def test_build_links_without_room_for_a_workspace(asq, side):
+    """Where the workspace does not fit the device, the binding takes the workspace-free call: its bits."""
+    import torch
+
+    dims = (16, 16, 16, 16)  # 264 MB of workspace
+    thin = torch.randn(65536 * 72, dtype=torch.float64, device="cuda",
+                       generator=torch.Generator("cuda").manual_seed(6)) * 0.3
+    want = _free_form(asq, dims, thin, 0.9)
+    fat, lng = torch.empty_like(thin), torch.empty_like(thin)
+    stream = torch.cuda.Stream() if side else None
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    print(f"links without room side={side}", flush=True)
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
+    try:
+        asq.build_links(dims, thin, 0.9, fat=fat, lng=lng, stream=stream)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(fat, want[0]) and torch.equal(lng, want[1])
+
+
+def test_build_links_under_capture(asq):
+    """A captured call takes no workspace, which its replays would use after it is someone else's: every
+    replay gives the eager bits of the workspace-free call, with other work in between."""
+    import torch
+
+    dims = (6, 6, 4, 10)
+    thin = asq.links_to_device(synth.thin_links(dims, 0.4, seed=45).reshape(-1, 4, 3, 3))
+    want = _free_form(asq, dims, thin, 0.9)
+    fat, lng = torch.empty_like(thin), torch.empty_like(thin)
+    asq.build_links(dims, thin, 0.9, fat=fat, lng=lng)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    print("links under capture", flush=True)
+    with torch.cuda.graph(graph):
+        before = torch.cuda.memory_stats()["allocation.all.allocated"]
+        asq.build_links(dims, thin, 0.9, fat=fat, lng=lng)
+        assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    for k in range(3):
+        fat.zero_()
+        lng.zero_()
+        other = torch.randn(1 << 20, device="cuda")
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(fat, want[0]) and torch.equal(lng, want[1])
+        assert bool(torch.isfinite(other).all())
