@@ -10,6 +10,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <array>
 #include <map>
 #include <mutex>
@@ -104,6 +105,14 @@ int default_rtile(int link, int ncol) {
   if (link == LINK_F64_R18) return 2;
   return ncol >= 4 ? 4 : 2;
 }
+
+// How far from the best a candidate of the tuner may be to be timed further.  The LDS
+// form shortens a launch by up to 10 %, and wherever it was the best the same launch
+// without it was within 6 % of the best without it (44 configurations, 8^4 to 48^3 x 96,
+// 1 to 96 columns); launches repeat to a few percent.  First call of 12 FP64
+// columns at 16^3 x 32 with every LDS form, and every candidate timed twice, 220 ms, so
+// 109; of 96 FP16 columns at 20^3 x 64 4.6 and 2.2 s.
+constexpr float kTuneNear = 1.15f;
 
 bool tuning_on() {
   const char* e = getenv("ASQ_TUNE");
@@ -202,13 +211,6 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
       for (size_t q = 0; q < n; ++q)
         if ((cands[q] & 0xff) == 1 && variant_built(link, in, cands[q] | kStreamBit)) cands.push_back(cands[q] | kStreamBit);
     }
-    // and every pipelined candidate with the LDS window (windows too large for LDS are
-    // refused; a candidate that fails to launch is skipped)
-    {
-      const size_t n = cands.size();
-      for (size_t q = 0; q < n; ++q)
-        if (variant_built(link, in, cands[q] | kLdsBit)) cands.push_back(cands[q] | kLdsBit);
-    }
     // launches of few blocks: the split form
     if ((long)g->nblk * ncol <= kSplitMaxBlocks) cands.push_back(kSplitCode);
     // The solver runs D_oe forwards and D_eo backwards, so each sweep starts on
@@ -223,35 +225,45 @@ int tune_dslash(const asq_gauge* g, int link, int in, int ncol, const void* in_b
       }
       return ok;
     };
-    for (int r : cands) {
+    // A candidate whose first timing is far from the best is not timed again, and its
+    // LDS form is not tried (kTuneNear).
+    auto time_one = [&](int r) {
       const int cols = tile_cols(r);
-      if (cols > 1 && cols > ncol) continue;  // a wider tile than the batch only wastes lanes
-      if (!pair(r)) continue;  // warm-up
-      // a candidate whose timing fails is skipped
       float ms = 1e30f;
-      bool ok = true;
-      for (int rep = 0; rep < 2 && ok; ++rep) {
-        ok = hipEventRecord(e0, s) == hipSuccess && pair(r) && pair(r) && hipEventRecord(e1, s) == hipSuccess &&
-             hipEventSynchronize(e1) == hipSuccess;
+      if (cols > 1 && cols > ncol) return ms;  // a wider tile than the batch only wastes lanes
+      if (!pair(r)) return ms;  // warm-up
+      // the UPDATE epilogue also keeps r, x and the direction of every column of
+      // the tile live: the 12-column tile loses occupancy there that the plain
+      // loop timed here does not show
+      const bool three_ok = cols != 3 || (long)g->nblk * ((ncol + 2) / 3) >= kThreeUpdateMinBlocks;
+      const bool update_ok = cols <= 8 && three_ok;
+      for (int rep = 0; rep < 2; ++rep) {
         float t = 0;
-        ok = ok && hipEventElapsedTime(&t, e0, e1) == hipSuccess;
-        if (ok && t < ms) ms = t;
+        // a candidate whose timing fails is skipped
+        if (hipEventRecord(e0, s) != hipSuccess || !pair(r) || !pair(r) || hipEventRecord(e1, s) != hipSuccess ||
+            hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&t, e0, e1) != hipSuccess)
+          return 1e30f;
+        if (t < ms) ms = t;
+        if (ms > kTuneNear * best_ms && !(update_ok && ms <= kTuneNear * best_update_ms)) break;
       }
-      if (!ok) continue;
       if (log_enabled()) fprintf(stderr, "[asq] tune %s R=%d %.4f ms\n", kp.c_str(), r, ms / 4);
       if (ms < best_ms) {
         best_ms = ms;
         best = r;
       }
-      // the UPDATE epilogue also keeps r, x and the direction of every column of
-      // the tile live: the 12-column tile loses occupancy there that the plain
-      // loop timed here does not show
-      const bool three_ok = cols != 3 || (long)g->nblk * ((ncol + 2) / 3) >= kThreeUpdateMinBlocks;
-      if (cols <= 8 && three_ok && ms < best_update_ms) {
+      if (update_ok && ms < best_update_ms) {
         best_update_ms = ms;
         best_update = r;
       }
-    }
+      return ms;
+    };
+    std::vector<float> took;
+    for (int r : cands) took.push_back(time_one(r));
+    // the pipelined candidates near the best with the LDS window (windows too large for
+    // LDS are refused; a candidate that fails to launch is skipped)
+    const float near_ms = kTuneNear * std::max(best_ms, best_update_ms);
+    for (size_t q = 0; q < cands.size(); ++q)
+      if (took[q] <= near_ms && variant_built(link, in, cands[q] | kLdsBit)) time_one(cands[q] | kLdsBit);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
   }
