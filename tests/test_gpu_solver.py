@@ -639,3 +639,28 @@ def test_breakdown_leaves_the_other_columns_alone(asq, monkeypatch, mode, form):
     for c in (1, 2):
         assert res.stats[c]["status"] == 0 and res.stats[c]["iters"] == want.stats[c]["iters"]
         assert x[c].tobytes() == xw[c].tobytes()
+
+
+# 262 site blocks, the last one ragged: a second partial per thread; 1024, the most that are folded: four
+@pytest.mark.parametrize("dims", [(14, 18, 14, 38), (16, 16, 16, 128)])
+@pytest.mark.parametrize("mode,form", [("f64", "split"), ("mixed32", "split"), ("mixed32", "three"), ("mixed16", "three")])
+def test_folded_scalars_over_many_site_blocks(asq, monkeypatch, dims, mode, form):
+    """The split form's partials per wave and the three-column tile's folded alpha, where a thread sums
+    several partials of a column: the bits of the plain form with scalar launches."""
+    monkeypatch.setenv("ASQ_TUNE", "0")
+    masses = [0.3, 0.4, 0.5]
+    fat, lng = gauge_arrays(dims, 0.3, 7)
+    g = asq.Gauge(dims, fat, lng, precs=("f64", "f32"), recon=18)
+    b = synth.make_sources(dims, 3, 98)
+    monkeypatch.setenv("ASQ_FOLD_ALPHA", "0")
+    monkeypatch.setenv("ASQ_FOLD_BETA", "0")
+    x, want = _solve(asq, g, masses, b, mode)
+    monkeypatch.setenv("ASQ_VARIANT", str(1 | 1 << 10 if form == "split" else asq.variant_code(6, True, 0) | 1 << 9))
+    for fold in ("0", "1"):
+        print(f"folds {fold} {dims} {mode} {form}", flush=True)
+        monkeypatch.setenv("ASQ_FOLD_ALPHA", fold)
+        monkeypatch.setenv("ASQ_FOLD_BETA", fold)
+        y, got = _solve(asq, g, masses, b, mode)
+        assert got.rc == 0 and want.rc == 0
+        assert [s["iters"] for s in got.stats] == [s["iters"] for s in want.stats]
+        assert y.tobytes() == x.tobytes()
