@@ -43,6 +43,9 @@ PEAK_FP64_TFLOPS = 78.6
 # SU(3) products per (site, direction) of the link construction in three stages of shared
 # staples: 12 + 24 + 24 for the fat link, 2 for the long link; 198 flops each
 LINK_BUILD_PRODUCTS = 62
+# bytes that its four launches move past L2 at 20^3 x 64 (FETCH_SIZE and WRITE_SIZE, calibrated on a
+# copy): transpose 0.59, stages 2.45 + 4.20 + 3.36 GB.  They bound it; arithmetic is 0.32 ms.
+LINK_BUILD_MISS_BYTES = 10.61e9
 METRIC = "asqtad Dslash HBM GB/s; CG time-to-1e-10 at 20^3x64; solves/s + p99 latency"
 
 LINK_BYTES = {"f64": 144, "f32": 72, "f32r12": 48, "f16r12": 24}
@@ -890,11 +893,13 @@ def run_asqtad(args, asq, torch):
            "unit": "ms per link construction", "higher_is_better": False, "dtype": "f64", "data": "synthetic",
            "u0": u0, "plaquette": plaq, "u0_from_plaquette": plaq ** 0.25, "plaquette_ms": t_plaq * 1e3,
            "config": {"workload": "asqtad_20x20x20x64", "dims": list(dims), "eps": w["eps"]},
-           "roofline": {"bound": "alu", "achieved": tf, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
-                        "frac": tf / PEAK_FP64_TFLOPS, "traffic": None,
+           "roofline": {"bound": "hbm", "achieved": LINK_BUILD_MISS_BYTES / dt / 1e9, "peak": PEAK_HBM_GBS,
+                        "unit": "GB/s", "frac": LINK_BUILD_MISS_BYTES / dt / 1e9 / PEAK_HBM_GBS,
+                        "traffic": LINK_BUILD_MISS_BYTES,
                         "kernel": "asqtad_build_links_work: transpose and the three stages (FP64), "
                                   "timed together",
-                        "flops_per_call": flops, "ms_per_call": dt * 1e3},
+                        "basis": "counter-measured L2 misses, part of them served by the 256 MB memory-side cache",
+                        "tflops": tf, "flops_per_call": flops, "ms_per_call": dt * 1e3},
            "solve_mixed32": {"ms": secs * 1e3, "time_to_solution": time_stats(times), "iters": st["iters"],
                              "reliable_updates": st["reliable_updates"], "true_resid": st["true_resid"],
                              "mass": mass},

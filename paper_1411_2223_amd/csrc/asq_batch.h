@@ -38,13 +38,15 @@ struct Batch {
   int link = 0;        // link tier of the iterated Dslash
   int rt_sloppy_norm = 1, rt_sloppy_update = 1, rt64_plain = 1, rt64_resid = 1;
   bool sweep = true;   // D_eo walks the lattice backwards (MALL reuse of the links)
-  bool fold_alpha = false;  // D_eo forms alpha itself (few columns): no scalar launch between the Dslashes
+  bool fold_alpha = false;  // D_eo forms alpha itself (narrow tiles): no scalar launch between the Dslashes
   bool fold_beta = false;   // the direction update forms beta itself: no scalar launch after D_eo
   ColState* st = nullptr;   // the column states between blocks of iterations
   ColState* st2 = nullptr;  // second copy: with fold_beta, iterations alternate between st and st2
-  double* partials = nullptr;    // [ncol][nblk] partials of |r|^2 (D_eo update, residual, init)
-  double* partials_p = nullptr;  // [ncol][nblk] partials of |p|^2 (direction update)
-  double* partials_t = nullptr;  // [ncol][nblk] partials of |D_oe p|^2
+  // block partials; partials and partials_t hold up to kWaves per site block, which the
+  // split form of the Dslash writes (partial_sub of the launch's variant; else one)
+  double* partials = nullptr;    // [ncol][nblk][sub] of |r|^2 (D_eo update, residual; init: one)
+  double* partials_p = nullptr;  // [ncol][nblk] of |p|^2 (direction update)
+  double* partials_t = nullptr;  // [ncol][nblk][sub] of |D_oe p|^2
   double* b = nullptr;  // F64 [ncol][3][half][2]
   double* x = nullptr;
   void* xs = nullptr;  // F32 accumulator of x between reliable updates (mixed modes)

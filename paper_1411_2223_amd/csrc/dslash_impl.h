@@ -16,10 +16,11 @@
 //   EPI_NORM    out = D in and block partials of |out|^2: with t = D_oe p this
 //               gives <p, A p> = a |p|^2 + |t|^2, since D_eo = -D_oe^dag
 //   EPI_UPDATE  Ap = a p - D_eo t kept in registers; r -= alpha Ap and
-//               x += alpha p at the site; block partials of |r|^2.  With few
-//               columns every block sums the <p, A p> partials itself (same
-//               order and tree as the scalar kernel, so the same alpha) and the
-//               scalar launch between the two Dslash launches disappears
+//               x += alpha p at the site; block partials of |r|^2.  With
+//               narrow tiles (kFoldAlphaMaxTile) on up to 4 kBlock site blocks
+//               every block sums the <p, A p> partials itself (same order and
+//               tree as the scalar kernel, so the same alpha) and the scalar
+//               launch between the two Dslash launches disappears
 //   EPI_RESID   out = b - a y + D in in FP64 (the true residual), stored in the
 //               output tier as the new iterated r; block partials of |out|^2
 #pragma once
@@ -307,8 +308,7 @@ __global__ void __launch_bounds__(kBlock) dslash_kernel(const DslashArgs A) {
   }
   if (!any) return;  // uniform over the block
   // alpha of each column for the UPDATE epilogue, formed in this launch from the
-  // partials for the narrow tiles of small batches (same order and tree as the
-  // scalar kernel): up to 4 kBlock partials per column (the launch refuses more),
+  // partials for narrow tiles (same order and tree as the scalar kernel): up to 4 kBlock partials per column (the launch refuses more),
   // loaded here and summed after the hop loop, which hides their latency.
   [[maybe_unused]] double alpha[R];
   [[maybe_unused]] double qa[R][4], qb[R][4];
@@ -753,9 +753,10 @@ int pick_r(int rtile, const DslashArgs& a, hipStream_t s) {
   }
   if (rtile & kLdsBit) {
     // the LDS window: pipelined loop; one column with ordinary or streamed links, or a
-    // tile of 2 to 12 columns.  (On the canonical layouts only the tuner takes it:
-    // 96 FP16 columns at 20^3 x 64 0.775 -> 0.718 ms, 12 with 16-bit links at 48^3 x 96
-    // 1.97 -> 1.89, 12 FP64 columns at 16^3 x 32 68 -> 65 us.)
+    // tile of 2 to 12 columns.  (On the canonical layouts only the tuner takes it.
+    // Public calls on four fields in turn, the best code without it and with it: 96 FP16
+    // columns at 20^3 x 64 772 -> 714 us, 12 with 16-bit links at 48^3 x 96 1.96 -> 1.88 ms,
+    // 12 FP64 columns at 16^3 x 32 77 -> 72 us.)
     constexpr bool f64_links = std::is_same<Link, LinkF64R18>::value || std::is_same<Link, LinkF64F32>::value;
     if (!pipe) return ASQ_EINVAL;
     if (rtile & kStreamBit) {

@@ -332,13 +332,13 @@ __global__ void __launch_bounds__(256) fatten_kernel(const FattenArgs A) {
 //   F_mu(x)   = c1 U_mu(x) + sum_+-nu T_d(v_nu + cL T_d(U_mu))(x)           (stage 3)
 // 12 + 24 + 24 = 60 products per (site, mu) instead of 156, and what bounds a stage is
 // no longer arithmetic (0.32 ms in all at the FP64 peak, 20^3 x 64) but the staples'
-// operands past the 4 MB L2: 9.3 GB of L2 misses, at 4.5 TB/s with two waves per SIMD
-// (three or four spill, twice the time).  20^3 x 64: 3.3 -> 2.2 ms; stage 1 with the
+// operands past the 4 MB L2: 10.0 GB of L2 misses (counters), at 4.8 TB/s with two waves
+// per SIMD (three or four spill, twice the time).  20^3 x 64: 3.3 -> 2.2 ms; stage 1 with the
 // long links 0.53, stage 2 0.79, stage 3 0.77, the transpose 0.10.
 constexpr long kStageMaxSites = (1L << 28) - 1;  // site indices, and differences of them, in 32 bits
 // All four directions per launch, 4032 workspace bytes per site, up to 4 GiB of
-// workspace; beyond, one direction at a time in 1440 bytes per site (0.46 ms more
-// at 20^3 x 64, measured with a thread per (site, mu)).
+// workspace; beyond, one direction at a time in 1440 bytes per site (2.64 instead
+// of 2.20 ms at 20^3 x 64).
 constexpr long kStageAllMuSites = (4L << 30) / 4032;
 struct StageArgs {
   int d[4], s[4];       // extents and lexicographic strides
