@@ -70,13 +70,11 @@ __host__ __device__ inline void finalize_column(ColState& S, double s, int op) {
       break;
     case OP_BETA: {
       if (!S.active) break;  // stopped by OP_ALPHA
-      if (S.status == ASQ_ENAN) {  // by alpha_step: s means nothing
-        S.active = 0;
-        break;
-      }
-      S.iters += 1;
-      S.pbuf ^= 1;  // the new direction becomes current
-      if (!finite) {
+      // after a breakdown noted by alpha_step s means nothing and the step did not happen
+      const int went = S.status != ASQ_ENAN;
+      S.iters += went;
+      S.pbuf ^= went;  // the new direction becomes current
+      if (!finite || !went) {
         S.status = ASQ_ENAN;
         S.active = 0;
         break;
