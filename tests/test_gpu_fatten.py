@@ -228,26 +228,27 @@ def _free_form(asq, dims, thin, u0):
 
 
 @pytest.mark.parametrize("side", [False, True])
-def test_build_links_without_room_for_a_workspace(asq, side):
-    """Where the workspace does not fit the device, the binding takes the workspace-free call: its bits."""
+def test_build_links_without_room_for_a_workspace(asq, monkeypatch, side):
+    """Where the device has no room for the workspace, the binding takes the workspace-free call: its bits."""
     import torch
 
-    dims = (16, 16, 16, 16)  # 264 MB of workspace
-    thin = torch.randn(65536 * 72, dtype=torch.float64, device="cuda",
+    dims = (8, 6, 10, 12)
+    thin = torch.randn(5760 * 72, dtype=torch.float64, device="cuda",
                        generator=torch.Generator("cuda").manual_seed(6)) * 0.3
     want = _free_form(asq, dims, thin, 0.9)
-    fat, lng = torch.empty_like(thin), torch.empty_like(thin)
+    asked = []
+
+    def full(n, device="cuda"):
+        asked.append(n)
+        raise torch.OutOfMemoryError("no room")
+
+    monkeypatch.setattr(asq, "empty_bytes", full)
     stream = torch.cuda.Stream() if side else None
     torch.cuda.synchronize()
-    torch.cuda.empty_cache()
-    total = torch.cuda.get_device_properties(0).total_memory
     print(f"links without room side={side}", flush=True)
-    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + (64 << 20)) / total)
-    try:
-        asq.build_links(dims, thin, 0.9, fat=fat, lng=lng, stream=stream)
-    finally:
-        torch.cuda.set_per_process_memory_fraction(1.0)
+    fat, lng = asq.build_links(dims, thin, 0.9, stream=stream)
     torch.cuda.synchronize()
+    assert asked == [28 * 5760 * 144]
     assert torch.equal(fat, want[0]) and torch.equal(lng, want[1])
 
 
