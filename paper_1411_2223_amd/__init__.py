@@ -306,7 +306,7 @@ def build_links(dims, thin_dev, u0=1.0, fat=None, lng=None, stream=None):
     layout (see links_to_device); fat and lng are allocated when not given.
     Returns (fat, lng); the work is enqueued on the stream.  Its workspace (4032 bytes per site up to
     4 GiB, 1440 beyond) stays with PyTorch's caching allocator; where none can be had, and in a stream
-    capture, the links come from the call that takes none (1.5 times the time, equal to rounding).
+    capture, the links come from the call that takes none (1.4 times the time, equal to rounding).
     """
     torch = _torch()
     load()
